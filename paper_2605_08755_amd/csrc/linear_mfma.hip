@@ -24,19 +24,12 @@
 // kernel adds in order); four or eight tiles per block walking K one quad at
 // a time, two quads ahead (many tiles, longer rows).  Every reduction order
 // is fixed, so results are deterministic.
-#include <type_traits>
-#include <utility>
-
-#include "laq_internal.h"
+#include "mfma_util.h"
 
 namespace laq {
 
 namespace {
 
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kBufferFlagsM = 0x00020000;
 // Cache policy of the weight loads.  A lane's 16-byte load covers four groups
 // of one row and plane, so one load instruction uses half of each 128-byte
 // line it touches and the next quad's load uses the other half.  With the
@@ -48,22 +41,8 @@ constexpr int kBufferFlagsM = 0x00020000;
 constexpr int kWeightPolicy = 0;    // plain
 constexpr int kWeightPolicyNT = 2;  // non-temporal
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, kBufferFlagsM);
-}
-
 __device__ __forceinline__ uint32_t pk_add_f16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b));
-}
-
-// (a & m) | c in one v_and_or_b32.  The mask lives in a scalar register and
-// the magic constant in a vector register (a VOP3 instruction takes no
-// literal on this target, and at most one scalar operand); left to itself the
-// compiler emits a v_and_b32 and a v_or_b32 with literals instead.
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t m, uint32_t c) {
-  uint32_t r;
-  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(m), "v"(c));  // mask from a scalar register
-  return r;
 }
 
 // fp16 bit patterns of -(2^(10-p) + z) in both halves, for the field
@@ -110,11 +89,6 @@ __device__ __forceinline__ void unpack_chunk_exact(const uint32_t (&w)[BITS], ui
   }
 }
 
-__device__ __forceinline__ half8_t frag(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-  return __builtin_bit_cast(half8_t, u32x4v{a, b, c, d});
-}
-
 // Fragment reads from an LDS slab that direct-to-LDS loads fill, written as
 // inline assembly on purpose: the compiler's wait insertion treats any LDS
 // read that follows a direct-to-LDS load as dependent on every such load in
@@ -135,40 +109,9 @@ __device__ __forceinline__ void lds_wait(u32x4 (&f)[4]) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
 }
 
-// s_waitcnt vmcnt(N) (other counters unconstrained), N a compile-time constant <= 63.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (((N >> 4) & 3) << 14));
-}
-
-// f(std::integral_constant<int, I>{}) for I = 0 .. N-1, in order.
-template <typename F, int... Is>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
 // Loads of dead lanes (rows past M, columns past K, groups past G) OR bit
 // 31 into their offsets: that is past every buffer extent, so the load
 // returns zero and moves no data.
-
-// 4 x 4 transpose across the four 16-lane quarters of a wave: on entry
-// register c of quarter j holds element (j, c); on exit register j of
-// quarter c holds it.  Two rounds of lane-half swaps (32 lanes, then 16).
-__device__ __forceinline__ void transpose_quarters(uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
-  auto a = __builtin_amdgcn_permlane32_swap(r0, r2, false, false);
-  auto b = __builtin_amdgcn_permlane32_swap(r1, r3, false, false);
-  auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-  auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-  r0 = c[0];
-  r1 = c[1];
-  r2 = d[0];
-  r3 = d[1];
-}
 
 // Block: TW tiles of 16 weight rows and every group of them.  Work item of a
 // wave: the four consecutive groups 4Q..4Q+3 (a "quad") of all TW tiles; the
@@ -1018,6 +961,26 @@ SplitPlan mfma_split_plan(int M, int64_t N, int G) {
   return p;
 }
 
+// Where keeping the activations in registers over many tiles (linear_stream.hip)
+// is the faster way: enough (tile, quad) units that a block walks several
+// tiles, more of them for fewer activation rows, whose slabs cost the
+// tile-by-tile kernels less.  Measured on MI355X, tile by tile -> stream, W3:
+// M = 16: 8192 x 4096 (4096 units) 9.4 -> 6.4 us, 5120 x 8192 (5120) 13.9 -> 11.5,
+// 10240 x 5120 (6400) 15.5 -> 11.0, 51200 x 5120 39.1 -> 28.2, but 2560 x 6144
+// (1920) 6.4 -> 7.0; M = 8: 5120 x 8192 11.1 -> 9.9, 10240 x 5120 10.8 -> 9.8, but
+// 8192 x 4096 6.9 -> 7.5, 19456 x 2560 (6080) 9.3 -> 10.1; M = 4: 24576 x 4096
+// (12288) 13.9 -> 11.8, 51200 x 5120 34.5 -> 26.4, 5120 x 8192 10.4 -> 8.9 (rows past
+// the one-wave-per-quad kernel's ten quads), but 30000 x 3200 (13125) 14.4 -> 14.9,
+// 10240 x 5120 9.8 -> 9.6, 8192 x 4096 6.1 -> 6.8.
+bool stream_pays(int M, int64_t tiles, int nq) {
+  const int64_t units = tiles * nq;
+  if (nq < 5) return false;
+  if (nq > kQuadWaveMax) return units >= 4096;
+  if (M > 8) return units >= (nq > 5 ? 4096 : 8192);
+  if (M > 4) return units >= 6144;
+  return units >= (nq >= 8 ? 12288 : 16384);
+}
+
 template <int BITS>
 hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const uint16_t* scales,
                               const uint8_t* zeros, uint16_t* y, int M, int64_t N, int64_t K,
@@ -1026,6 +989,9 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
   const int G = (int)(K / 128);
   const int nq = (G + 3) / 4;
   const int64_t tiles = (N + 15) / 16;
+  if (stream_pays(M, tiles, nq))
+    if (const StreamPlan st = stream_plan(BITS, M, N, G); st.W > 0)
+      return launch_linear_stream<BITS>(st, x, qweight, scales, zeros, y, M, N, G, stream, ev);
   // Many tiles, rows of at most five quads, M > 4 (W4: M > 8; at M <= 8 the
   // one-tile blocks below are faster for W4): three tiles per block share
   // the quads' slabs, one wave per (tile, quad).

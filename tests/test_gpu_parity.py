@@ -526,6 +526,38 @@ def test_matrix_core_walk_ragged():
     torch.cuda.empty_cache()
 
 
+STREAM_SHAPES = [(8200, 8192, (3, 8, 16)), (9003, 6528, (4, 9)), (26003, 2176, (8, 16)), (65541, 2560, (3, 16)),
+                 (16389, 3968, (8, 12)), (24581, 4096, (4, 5)), (10241, 5120, (8, 13))]
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("N,K,Ms", STREAM_SHAPES)
+def test_matrix_core_stream(bits, N, K, Ms):
+    """Activations in registers over many tiles: 16 quads (K = 8192: the
+    activations staged in one, two or four phases by M; W4 at M = 16 with one
+    buffer of partials), 13 and 8 quads with partial last ones (51 and 31
+    groups), an odd count of quads whose last one has a single group (K =
+    2176), three tiles per step (K = 2560), whole lines (G % 8 == 0: K = 4096,
+    5120, 8192) and part lines, ragged last tiles and last steps with idle
+    tiles.  Sampled rows and the last rows against the oracle; repeated calls
+    bit-identical; nothing written past the output."""
+    say("mfma stream", bits, N, K)
+    rng = np.random.default_rng(N + bits)
+    w = inputs.weights(N, K, cfg=24, layer=bits, proj=K % 97)
+    rows = np.concatenate([np.arange(16), np.sort(rng.choice(N - 64, 48, replace=False)) + 16, np.arange(N - 40, N)])
+    codes, qw, s, z = oracle_packed(np.ascontiguousarray(w[rows]), bits)
+    q, sd, zd = laq.quantize(to_dev(w), bits)
+    for M in Ms:
+        x = inputs.activations(M, K, cfg=24, layer=M)
+        ybuf = torch.full((M * N + 64,), 3.0, dtype=torch.float16, device=DEV)
+        y = laq.linear(to_dev(x), q, sd, zd, bits, out=ybuf[:M * N].view(M, N))
+        y2 = laq.linear(to_dev(x), q, sd, zd, bits)
+        torch.cuda.synchronize()
+        r = linear_check(y.cpu().numpy()[:, rows], oracle.linear(x, codes, s, z))
+        assert r["ok"], (M, r)
+        assert torch.equal(y, y2) and torch.all(ybuf[M * N:] == 3.0), M
+
+
 SPLIT_SHAPES = [(5120, 25600), (100, 25088), (3, 20608), (1030, 20480)]
 
 
