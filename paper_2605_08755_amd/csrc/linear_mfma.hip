@@ -693,19 +693,23 @@ __device__ __forceinline__ u32x4 lds_read_b128_off(uint32_t addr) {
   return r;
 }
 
-template <int BITS, int MT, bool LOWREG>
-__global__ __launch_bounds__(64 * kQuadWaveMax) __attribute__((amdgpu_waves_per_eu(LOWREG ? 8 : 1))) void
-linear_mfma_quad_wave_kernel(
+// CLDS: the codes come through LDS (request_quad: a quarter of the register
+// path's address work, no transposes), for blocks whose LDS then still leaves
+// every compute unit its share of the tiles; otherwise they are loaded into
+// registers.  (Measured on MI355X, M = 4 / 16: 2560 x 4096 3.90 -> 3.58 us /
+// 4.67 -> 4.11 us, 2560 x 5120 4.24 -> 3.98 us at M = 4; 6144 x 2560 at M = 16,
+// 384 tiles and one block per compute unit instead of two, 4.98 -> 6.65 us.)
+// GROUP: waves past the row's quads (a group's shorter rows) only join the barrier.
+template <int BITS, int MT, bool LOWREG, bool CLDS, bool GROUP>
+__device__ __forceinline__ void quad_wave_block(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ qw, const uint16_t* __restrict__ scales,
-    const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, int M, int N, int G, int nblocks) {
+    const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, int M, int N, int G, int b, int nwaves) {
   static_assert(MT == 4 || MT == 8 || MT == 16, "slab rows");
   typedef __attribute__((address_space(3))) void lds_void;
   extern __shared__ u32x4 wslab[];  // [W][MT rows][64 pieces]; afterwards [W][4][64] fp32 partials
   constexpr int WL = BITS + 2;      // weight loads per lane
-  const int b = xcd_block(nblocks);
-  if (b >= nblocks) return;  // idle slot of the XCD-rounded grid (the whole block leaves)
   const int K = 128 * G;
-  const int W = (G + 3) >> 2;  // one wave per quad (the block size)
+  const int W = (G + 3) >> 2;  // one wave per quad
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wave's quad
   const int nl = lane & 15;  // weight row / activation row / result column
@@ -720,95 +724,101 @@ linear_mfma_quad_wave_kernel(
   const __amdgpu_buffer_rsrc_t sr = rsrc(scales + row0 * G, (uint32_t)rows * G * 2);
   const __amdgpu_buffer_rsrc_t zr = rsrc(zeros + row0 * G, (uint32_t)rows * G);
 
-  // 1. The slab (MT direct loads), then the weights.  The waits below count
-  //    outstanding loads in this issue order (scheduling barriers).
+  if (!GROUP || wave < W) {
+    // 1. The slab (MT direct loads), then the weights.  The waits below count
+    //    outstanding loads in this issue order (scheduling barriers).
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    const int col = 512 * wave + 8 * (lane ^ (m & 7));
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void*)(sl + m * 64), 16,
-                                             (uint32_t)(m * K + col) * 2 | (uint32_t)!(m < M && col < K) << 31, 0,
-                                             0, 0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  const QuadWeights<BITS> qwt = load_quad<BITS, kWeightPolicy>(qr, sr, zr, nl, j, wave, G, true);
-  __builtin_amdgcn_sched_barrier(0);
+    for (int m = 0; m < MT; ++m) {
+      const int col = 512 * wave + 8 * (lane ^ (m & 7));
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void*)(sl + m * 64), 16,
+                                               (uint32_t)(m * K + col) * 2 | (uint32_t)!(m < M && col < K) << 31, 0,
+                                               0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    char* const unit = reinterpret_cast<char*>(wslab) + W * MT * 1024 + wave * unit_bytes(BITS);
+    QuadWeights<BITS> qwt;
+    if constexpr (CLDS) request_quad<BITS, kWeightPolicy>(unit, qr, sr, zr, lane, wave, G, true);
+    else qwt = load_quad<BITS, kWeightPolicy>(qr, sr, zr, nl, j, wave, G, true);
+    __builtin_amdgcn_sched_barrier(0);
 
-  // 2. The A fragments: group gi, MFMA jj reads piece 16 gi + 4 j + jj of the
-  //    lane's activation row (stored at position piece ^ (row & 7)).
-  wait_vmcnt<WL>();
-  __builtin_amdgcn_sched_barrier(0);
-  const int arow = nl & (MT - 1);
-  const uint32_t abase = lds_addr(sl + arow * 64);
-  const int swz = arow & 7;
-  uint32_t aoff[4];
+    // 2. The A fragments: group gi, MFMA jj reads piece 16 gi + 4 j + jj of the
+    //    lane's activation row (stored at position piece ^ (row & 7)).
+    wait_vmcnt<WL>();
+    __builtin_amdgcn_sched_barrier(0);
+    const int arow = nl & (MT - 1);
+    const uint32_t abase = lds_addr(sl + arow * 64);
+    const int swz = arow & 7;
+    uint32_t aoff[4];
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) aoff[jj] = abase + 16 * ((4 * j + jj) ^ swz);
-  //    Read up front (64 registers) unless LOWREG, which reads each group's
-  //    four fragments just before its MFMAs so the kernel fits in 64 VGPRs
-  //    (8 waves per SIMD instead of 5).
-  u32x4 af[4][4];
-  if constexpr (!LOWREG) {
+    for (int jj = 0; jj < 4; ++jj) aoff[jj] = abase + 16 * ((4 * j + jj) ^ swz);
+    //    Read up front (64 registers) unless LOWREG, which reads each group's
+    //    four fragments just before its MFMAs so the kernel fits in 64 VGPRs
+    //    (8 waves per SIMD instead of 5).
+    u32x4 af[4][4];
+    if constexpr (!LOWREG) {
+      static_for<4>([&](auto gc) {
+        constexpr int gi = decltype(gc)::value;
+        static_for<4>([&](auto jc) {
+          constexpr int jj = decltype(jc)::value;
+          af[gi][jj] = lds_read_b128_off<256 * gi>(aoff[jj]);
+        });
+      });
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi) lds_wait(af[gi]);
+    }
+
+    // 3. Quarter transposes (chunk j of group 4q + gi in component gi), exact
+    //    (q - z) pairs, four MFMAs per group, scale.
+    wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t cw[4][BITS];
+    u32x4 sc, zc;
+    if constexpr (CLDS) {
+      read_quad<BITS>(cw, sc, zc, lds_byte(unit), lane);
+    } else {
+#pragma unroll
+      for (int p = 0; p < BITS; ++p) {
+        uint32_t t0 = qwt.w[p][0], t1 = qwt.w[p][1], t2 = qwt.w[p][2], t3 = qwt.w[p][3];
+        transpose_quarters(t0, t1, t2, t3);
+        cw[0][p] = t0, cw[1][p] = t1, cw[2][p] = t2, cw[3][p] = t3;
+      }
+      uint32_t t0 = qwt.s | (qwt.z << 16), t1 = t0, t2 = t0, t3 = t0;
+      transpose_quarters(t0, t1, t2, t3);
+      sc = u32x4{t0, t1, t2, t3};
+      zc = u32x4{t0 >> 16, t1 >> 16, t2 >> 16, t3 >> 16};
+    }
+    float4_t yacc = float4_t{0.f, 0.f, 0.f, 0.f};
     static_for<4>([&](auto gc) {
       constexpr int gi = decltype(gc)::value;
-      static_for<4>([&](auto jc) {
-        constexpr int jj = decltype(jc)::value;
-        af[gi][jj] = lds_read_b128_off<256 * gi>(aoff[jj]);
-      });
+      if constexpr (LOWREG) {
+        static_for<4>([&](auto jc) {
+          constexpr int jj = decltype(jc)::value;
+          af[gi][jj] = lds_read_b128_off<256 * gi>(aoff[jj]);
+        });
+      }
+      uint32_t pr[16];
+      unpack_chunk_exact<BITS>(cw[gi], zc[gi], pr);
+      if constexpr (LOWREG) lds_wait(af[gi]);
+      float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const half8_t bf = frag(pr[4 * jj + 0], pr[4 * jj + 1], pr[4 * jj + 2], pr[4 * jj + 3]);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][jj]), bf, c, 0, 0, 0);
+      }
+      const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)(sc[gi] & 0xFFFFu));
+      yacc += s * c;
     });
+    float* part = reinterpret_cast<float*>(sl);  // [4][64], over the slab just read
 #pragma unroll
-    for (int gi = 0; gi < 4; ++gi) lds_wait(af[gi]);
+    for (int r = 0; r < 4; ++r) part[r * 64 + lane] = yacc[r];
   }
-
-  // 3. Quarter transposes (chunk j of group 4q + gi in component gi), exact
-  //    (q - z) pairs, four MFMAs per group, scale.
-  wait_vmcnt<0>();
-  __builtin_amdgcn_sched_barrier(0);
-  uint32_t wt[BITS][4];
-#pragma unroll
-  for (int p = 0; p < BITS; ++p) {
-    wt[p][0] = qwt.w[p][0];
-    wt[p][1] = qwt.w[p][1];
-    wt[p][2] = qwt.w[p][2];
-    wt[p][3] = qwt.w[p][3];
-    transpose_quarters(wt[p][0], wt[p][1], wt[p][2], wt[p][3]);
-  }
-  uint32_t szj[4];
-  szj[0] = szj[1] = szj[2] = szj[3] = qwt.s | (qwt.z << 16);
-  transpose_quarters(szj[0], szj[1], szj[2], szj[3]);
-  float4_t yacc = float4_t{0.f, 0.f, 0.f, 0.f};
-  static_for<4>([&](auto gc) {
-    constexpr int gi = decltype(gc)::value;
-    if constexpr (LOWREG) {
-      static_for<4>([&](auto jc) {
-        constexpr int jj = decltype(jc)::value;
-        af[gi][jj] = lds_read_b128_off<256 * gi>(aoff[jj]);
-      });
-    }
-    uint32_t w[BITS];
-#pragma unroll
-    for (int p = 0; p < BITS; ++p) w[p] = wt[p][gi];
-    uint32_t pr[16];
-    unpack_chunk_exact<BITS>(w, szj[gi] >> 16, pr);
-    if constexpr (LOWREG) lds_wait(af[gi]);
-    float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const half8_t bf = frag(pr[4 * jj + 0], pr[4 * jj + 1], pr[4 * jj + 2], pr[4 * jj + 3]);
-      c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][jj]), bf, c, 0, 0, 0);
-    }
-    const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)(szj[gi] & 0xFFFFu));
-    yacc += s * c;
-  });
-  float* part = reinterpret_cast<float*>(sl);  // [4][64], over the slab just read
-#pragma unroll
-  for (int r = 0; r < 4; ++r) part[r * 64 + lane] = yacc[r];
   __syncthreads();
 
   // 4. Outputs (row n, activation row m): the W waves' partials in order.
   //    Lane (n, j) of a wave held rows m = 4j .. 4j+3 of column n.
   const float* red = reinterpret_cast<const float*>(wslab);
   const int wstride = MT * 64 * 4;  // floats per wave region
-  for (int idx = threadIdx.x; idx < 256; idx += 64 * W) {
+  for (int idx = threadIdx.x; idx < 256; idx += 64 * nwaves) {
     const int r = idx >> 6;
     const int ln = idx & 63;
     float v = 0.0f;
@@ -817,6 +827,32 @@ linear_mfma_quad_wave_kernel(
     const int n = ln & 15;
     if (m < M && n < rows) y[(int64_t)m * N + row0 + n] = __builtin_bit_cast(uint16_t, (_Float16)v);
   }
+}
+
+template <int BITS, int MT, bool LOWREG, bool CLDS>
+__global__ __launch_bounds__(64 * kQuadWaveMax) __attribute__((amdgpu_waves_per_eu(LOWREG ? 8 : 1))) void
+linear_mfma_quad_wave_kernel(
+    const uint16_t* __restrict__ x, const uint32_t* __restrict__ qw, const uint16_t* __restrict__ scales,
+    const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, int M, int N, int G, int nblocks) {
+  const int b = xcd_block(nblocks);
+  if (b >= nblocks) return;  // idle slot of the XCD-rounded grid (the whole block leaves)
+  quad_wave_block<BITS, MT, LOWREG, CLDS, false>(x, qw, scales, zeros, y, M, N, G, b, (G + 3) >> 2);
+}
+
+// Several independent calls of rows of at most kQuadWaveMax quads in one
+// launch; the call of block b is picked with constant indices, as in the flat
+// kernel.  Blocks have the longest row's waves.
+template <int BITS, int MT, bool LOWREG>
+__global__ __launch_bounds__(64 * kQuadWaveMax) __attribute__((amdgpu_waves_per_eu(LOWREG ? 8 : 1))) void
+linear_mfma_quad_wave_group_kernel(const LinearGroup grp, int M) {
+  const int b = xcd_block(grp.blocks);
+  if (b >= grp.blocks) return;  // idle slot of the XCD-rounded grid
+  LinearCall c = grp.call[0];
+#pragma unroll
+  for (int j = 1; j < kMaxGroup; ++j)
+    if (j < grp.count && b >= grp.call[j].first_block) c = grp.call[j];
+  quad_wave_block<BITS, MT, LOWREG, false, true>(c.x, c.qw, c.scales, c.zeros, c.y, M, c.N, c.G, b - c.first_block,
+                                                 grp.waves);
 }
 
 // ---------------------------------------------------------------------------
@@ -1022,19 +1058,24 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
       // MI355X: Qwen3-4B gate|up at M = 4, 1216 tiles x 5 waves, 10.8 -> 8.6 us;
       // the smaller projections are 1-2 % faster with the fragments up front).
       const bool lowreg = tiles * nq > (int64_t)kQuadWaveResident;
-#define LAQ_QW(MTV)                                                                                               \
-  do {                                                                                                            \
-    if (lowreg)                                                                                                   \
-      launch(linear_mfma_quad_wave_kernel<BITS, MTV, true>, grid, blk, (uint32_t)lds, stream, ev, x, qweight,     \
-             scales, zeros, y, M, (int)N, G, nblocks);                                                            \
-    else                                                                                                          \
-      launch(linear_mfma_quad_wave_kernel<BITS, MTV, false>, grid, blk, (uint32_t)lds, stream, ev, x, qweight,    \
-             scales, zeros, y, M, (int)N, G, nblocks);                                                            \
+      // Codes through LDS while the blocks that then fit on the compute units
+      // still hold every tile at once.
+      const size_t lds_codes = lds + (size_t)nq * unit_bytes(BITS);
+      const bool codes_lds = !lowreg && tiles <= 256 * (int64_t)((size_t)kBlockLdsU4 * 16 / lds_codes);
+#define LAQ_QW_K(MTV, LRV, CLV, LDSV)                                                                             \
+  launch(linear_mfma_quad_wave_kernel<BITS, MTV, LRV, CLV>, grid, blk, (uint32_t)(LDSV), stream, ev, x, qweight, \
+         scales, zeros, y, M, (int)N, G, nblocks)
+#define LAQ_QW(MTV)                                            \
+  do {                                                         \
+    if (lowreg) LAQ_QW_K(MTV, true, false, lds);               \
+    else if (codes_lds) LAQ_QW_K(MTV, false, true, lds_codes); \
+    else LAQ_QW_K(MTV, false, false, lds);                     \
   } while (0)
       if (MT == 4) LAQ_QW(4);
       else if (MT == 8) LAQ_QW(8);
       else LAQ_QW(16);
 #undef LAQ_QW
+#undef LAQ_QW_K
       return hipGetLastError();
     }
   }
@@ -1108,6 +1149,26 @@ hipError_t launch_linear_mfma_group(LinearCall* calls, int count, int M, hipStre
   }
   grp.count = count;
   grp.blocks = (int)blocks;
+  // Rows of at most kQuadWaveMax quads: one wave per quad, as for one call.
+  // (Measured on MI355X, W4 at M = 4: gate and up 2 x 9728 x 2560 11.9 us on the
+  // VALU kernel, q, k, v 7.2 us.)
+  const int MT = M <= 4 ? 4 : M <= 8 ? 8 : 16;
+  const size_t lds = (size_t)nq_max * MT * 1024;
+  if (nq_max <= kQuadWaveMax && lds <= (size_t)kBlockLdsU4 * 16) {
+    grp.waves = nq_max;
+    const dim3 grid(xcd_grid(blocks)), blk(64 * nq_max);
+    const bool lowreg = blocks * nq_max > (int64_t)kQuadWaveResident;
+#define LAQ_QWG(MTV)                                                                                                  \
+  do {                                                                                                                \
+    if (lowreg) launch(linear_mfma_quad_wave_group_kernel<BITS, MTV, true>, grid, blk, (uint32_t)lds, stream, ev, grp, M); \
+    else launch(linear_mfma_quad_wave_group_kernel<BITS, MTV, false>, grid, blk, (uint32_t)lds, stream, ev, grp, M);  \
+  } while (0)
+    if (MT == 4) LAQ_QWG(4);
+    else if (MT == 8) LAQ_QWG(8);
+    else LAQ_QWG(16);
+#undef LAQ_QWG
+    return hipGetLastError();
+  }
   const int W = mfma_block_waves(M, nq_max);  // as for one call
   grp.waves = W;
   launch(linear_mfma_group_kernel<BITS>, dim3(xcd_grid(blocks)), dim3(64 * W), (uint32_t)W * M * kSlabRowU4 * 16,
