@@ -6,7 +6,9 @@
 // orders (deterministic).  Head dimension 128.
 #include <math.h>
 
-#include "laq_internal.h"
+#include <algorithm>
+
+#include "mfma_util.h"
 
 namespace laq {
 
@@ -454,6 +456,288 @@ __global__ __launch_bounds__(64 * R) void attn_qkv_partial_kernel(
   *reinterpret_cast<float2*>(wp + 2 + 2 * lane) = float2{oe, oo};
 }
 
+// The same over long contexts: a block of eight waves holds one key/value head
+// and a chunk of positions, each wave walking its own steps of 32 positions
+// with a running maximum, denominator and value sums; the eight results meet
+// in LDS and leave one partial record per query head and block, so a context
+// of 32768 has 32 records per head to combine instead of 512.
+//
+// What bounds it: the cache bytes.  The tile kernel above spends its time in
+// the vector ALU (per position and query head one lane's dot product and a
+// fused multiply-add per two dimensions); here both products run on the matrix
+// cores for all R query heads at once:
+//  - scores: q (rows: heads) x keys (columns: 16 positions), fp16 operands as
+//    v_dot2 took them.  Keys go memory -> LDS directly, four rows of 256 bytes
+//    per instruction, piece p of row r at position p ^ (r & 15), which spreads
+//    the operand reads over every bank.
+//  - value sums: probabilities x values by the fp32 16x16x4 instruction, so the
+//    probabilities stay in 32 bits.  Its operand (lane (n, j): one position j,
+//    one column n) lets values come straight into registers: lane (n, j) loads
+//    dimensions 8n .. 8n+7 of one row, four whole rows per instruction, and
+//    element e is the operand of the columns {8n + e}.
+// The next step's loads are in flight while a step is computed.  The token at
+// pos is not read back from the cache: wave 0 of the last chunk starts from it
+// (maximum its score, denominator 1, value sums its value row).
+constexpr int kFlashWaves = 8;
+constexpr int kFlashStep = 32;                           // positions per wave and step
+constexpr int kFlashRow = (kFlashStep + 4) * 4;          // bytes of a row of probabilities (4 words of padding)
+constexpr int kFlashKeys = kFlashStep * kHeadDim * 2;    // bytes of a step's keys
+constexpr int kFlashLds = kFlashWaves * (2 * kFlashKeys + 16 * kFlashRow) + 16 * kHeadDim * 2;
+
+template <int CTRL>
+__device__ __forceinline__ float row_max_step(float v) {
+  return fmaxf(v, dpp<CTRL>(v));
+}
+// Maximum / sum over the 16 lanes of a DPP row, in every lane of the row.
+__device__ __forceinline__ float row_max(float v) {
+  return row_max_step<0x140>(row_max_step<0x141>(row_max_step<0x4E>(row_max_step<0xB1>(v))));
+}
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  v += dpp<0x140>(v);
+  return v;
+}
+// Four 16-byte LDS reads (inline assembly: the compiler makes every LDS read
+// wait for all direct-to-LDS loads in flight, the next step's included).
+__device__ __forceinline__ void lds_read4(u32x4 (&f)[4], uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\t"
+      "ds_read_b128 %1, %5\n\t"
+      "ds_read_b128 %2, %6\n\t"
+      "ds_read_b128 %3, %7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
+      : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+      : "memory");
+}
+__device__ __forceinline__ void lds_put(uint32_t addr, float v) {
+  asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory");
+}
+
+template <int R>
+__device__ __forceinline__ void flash_block(
+    uint16_t* __restrict__ kc, uint16_t* __restrict__ vc, int S_max, int pos, const uint16_t* __restrict__ qkv,
+    const uint16_t* __restrict__ qw, const float* __restrict__ cs, float eps, int Hq, int chunk,
+    const uint16_t* __restrict__ kw, int Hkv, int T, float* __restrict__ ws) {
+  typedef __attribute__((address_space(3))) void lds_void;
+  extern __shared__ u32x4 flash_lds[];
+  char* const lds = reinterpret_cast<char*>(flash_lds);
+  const int g = blockIdx.x;
+  const int split = blockIdx.y;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, j = lane >> 4;
+  char* const keys = lds + w * 2 * kFlashKeys;
+  const uint32_t probs = lds_byte(lds + kFlashWaves * 2 * kFlashKeys + w * 16 * kFlashRow);
+  uint16_t* const q16 = reinterpret_cast<uint16_t*>(lds + kFlashWaves * (2 * kFlashKeys + 16 * kFlashRow));
+  const int p_first = split * chunk + w * kFlashStep;  // this wave's first step
+  const int p_end = min(pos, (split + 1) * chunk);     // positions below pos of this chunk
+
+  // rows below pos of this head; later rows are past the extent (zeros)
+  const __amdgpu_buffer_rsrc_t kr = rsrc(kc + (int64_t)g * S_max * kHeadDim, (uint32_t)pos * kHeadDim * 2);
+  const __amdgpu_buffer_rsrc_t vr = rsrc(vc + (int64_t)g * S_max * kHeadDim, (uint32_t)pos * kHeadDim * 2);
+  constexpr int kLoads = kFlashStep / 4;  // load instructions per step for the keys, and for the values
+  u32x4 vv[2][kLoads];
+  auto request = [&](auto bc, int p) {
+    constexpr int B = decltype(bc)::value;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int r = 4 * i + j;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void*)(keys + B * kFlashKeys + i * 1024), 16,
+                                               (uint32_t)(p + r) * 256 + 16 * (n ^ (r & 15)), 0, 0, 0);
+    }
+    // values of step k = 4 kk + i: positions 16 kk + 4 j + i
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k)
+      vv[B][k] = __builtin_amdgcn_raw_buffer_load_b128(
+          vr, (uint32_t)(p + 16 * (k >> 2) + 4 * j + (k & 3)) * 256 + 16 * n, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int kStride = kFlashWaves * kFlashStep;
+  if (p_first < p_end) request(std::integral_constant<int, 0>{}, p_first);
+
+  // Query heads: normalized, rotated and rounded to fp16 as the separate
+  // qk-norm-rope call stores them; rows past R are zero.
+  for (int h = w; h < 16; h += kFlashWaves) {
+    if (h < R) {
+      const uint16_t* qsrc = qkv + (int64_t)(g * R + h) * kHeadDim;
+      float a = h2f(qsrc[lane]), b = h2f(qsrc[lane + 64]);
+      norm_rope_pair(a, b, qw, cs, eps, lane);
+      q16[h * kHeadDim + lane] = f2h(a);
+      q16[h * kHeadDim + lane + 64] = f2h(b);
+    } else {
+      q16[h * kHeadDim + lane] = 0;
+      q16[h * kHeadDim + lane + 64] = 0;
+    }
+  }
+  // The new token's key and value (the last chunk's wave 0).
+  const bool own = split == T - 1 && w == 0;
+  uint16_t* const new_kv = reinterpret_cast<uint16_t*>(lds + kFlashWaves * 2 * kFlashKeys);  // wave 0's probabilities
+  if (own) {
+    const uint16_t* ksrc = qkv + (int64_t)(Hq + g) * kHeadDim;
+    const uint16_t* vsrc = ksrc + (int64_t)Hkv * kHeadDim;
+    float a = h2f(ksrc[lane]), b = h2f(ksrc[lane + 64]);
+    const uint16_t v0 = vsrc[lane], v1 = vsrc[lane + 64];
+    norm_rope_pair(a, b, kw, cs, eps, lane);
+    const int64_t crow = ((int64_t)g * S_max + pos) * kHeadDim;
+    const uint16_t k0 = f2h(a), k1 = f2h(b);
+    kc[crow + lane] = k0;
+    kc[crow + lane + 64] = k1;
+    vc[crow + lane] = v0;
+    vc[crow + lane + 64] = v1;
+    new_kv[lane] = k0;
+    new_kv[lane + 64] = k1;
+    new_kv[kHeadDim + lane] = v0;
+    new_kv[kHeadDim + lane + 64] = v1;
+  }
+  __syncthreads();
+
+  // q as matrix operand: lane (m, j), window i: dimensions 32 i + 8 j .. + 7 of head m.
+  u32x4 qa[4];
+  {
+    const uint32_t a = lds_byte(q16) + n * kHeadDim * 2 + 16 * j;
+    lds_read4(qa, a, a + 64, a + 128, a + 192);
+  }
+  constexpr float kScale = 0.08838834764831845f;  // 1 / sqrt(128)
+  // Running state of head 4j + r: maximum, this lane's part of the
+  // denominator, and value sums of dimensions 8n + e.
+  float m[4], l[4];
+  float4_t o[8];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) m[r] = -INFINITY, l[r] = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = float4_t{0.f, 0.f, 0.f, 0.f};
+  if (own) {
+    u32x4 f[4];
+    const uint32_t a = lds_byte(new_kv) + 16 * j;  // the key as every column
+    lds_read4(f, a, a + 64, a + 128, a + 192);
+    float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, qa[i]), __builtin_bit_cast(half8_t, f[i]), c, 0, 0, 0);
+    const uint32_t b = lds_byte(new_kv) + kHeadDim * 2 + 16 * n;
+    lds_read4(f, b, b, b, b);
+    const half8_t v = __builtin_bit_cast(half8_t, f[0]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m[r] = c[r] * kScale, l[r] = n == 0 ? 1.0f : 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = float4_t{(float)v[e], (float)v[e], (float)v[e], (float)v[e]};
+  }
+
+  // One step: `B` the buffers that hold it, `next` the number of load
+  // instructions issued after its own.
+  auto step = [&](auto bc, int p, bool more) {
+    constexpr int B = decltype(bc)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) wait_vmcnt<3 * kLoads>();  // the keys: this step's values and the next step's loads may be outstanding
+    else wait_vmcnt<kLoads>();
+    __builtin_amdgcn_sched_barrier(0);
+    float sc[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      u32x4 f[4];
+      const uint32_t a = lds_byte(keys + B * kFlashKeys) + (16 * t + n) * 256;
+      lds_read4(f, a + 16 * (j ^ n), a + 16 * ((4 + j) ^ n), a + 16 * ((8 + j) ^ n), a + 16 * ((12 + j) ^ n));
+      float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, qa[i]), __builtin_bit_cast(half8_t, f[i]), c, 0, 0, 0);
+      const bool valid = p + 16 * t + n < p_end;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sc[t][r] = valid ? c[r] * kScale : -INFINITY;
+    }
+    float alpha[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float mn = fmaxf(m[r], row_max(fmaxf(sc[0][r], sc[1][r])));  // finite: a step has a valid position
+      alpha[r] = expf(m[r] - mn);
+      m[r] = mn;
+      const float p0 = expf(sc[0][r] - mn), p1 = expf(sc[1][r] - mn);
+      l[r] = fmaf(l[r], alpha[r], p0 + p1);
+      const uint32_t row = probs + (4 * j + r) * kFlashRow + 4 * n;
+      lds_put(row, p0);
+      lds_put(row + 64, p1);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[e][r] *= alpha[r];
+    u32x4 pa[4];
+    const uint32_t a = probs + n * kFlashRow + 16 * j;  // lane (m, j): positions 16 kk + 4 j .. + 3 of head m
+    lds_read4(pa, a, a + 64, a, a + 64);
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+      const u32x4 pk = pa[k >> 2];
+      const uint32_t pb = (k & 3) == 0 ? pk.x : (k & 3) == 1 ? pk.y : (k & 3) == 2 ? pk.z : pk.w;
+      const float pf = __builtin_bit_cast(float, pb);
+      const half8_t v = __builtin_bit_cast(half8_t, vv[B][k]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(pf, (float)v[e], o[e], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int p = p_first; p < p_end; p += 2 * kStride) {
+    const bool more = p + kStride < p_end;
+    if (more) request(std::integral_constant<int, 1>{}, p + kStride);
+    step(std::integral_constant<int, 0>{}, p, more);
+    if (more) {
+      const bool again = p + 2 * kStride < p_end;
+      if (again) request(std::integral_constant<int, 0>{}, p + 2 * kStride);
+      step(std::integral_constant<int, 1>{}, p + kStride, again);
+    }
+  }
+
+  // The waves' results, in wave order: record (wave, head) of 128 value sums
+  // over the keys' place, maxima and denominators over the queries'.
+  __syncthreads();
+  float* const osum = reinterpret_cast<float*>(lds);                                               // [8][R][128]
+  float* const stat = reinterpret_cast<float*>(lds + kFlashWaves * 2 * kFlashKeys);                // [8][R][2]
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int h = 4 * j + r;
+    const float lt = row_sum(l[r]);
+    if (h < R) {
+      float* d = osum + (w * R + h) * kHeadDim + 8 * n;
+      *reinterpret_cast<float4_t*>(d) = float4_t{o[0][r], o[1][r], o[2][r], o[3][r]};
+      *reinterpret_cast<float4_t*>(d + 4) = float4_t{o[4][r], o[5][r], o[6][r], o[7][r]};
+      if (n == 0) {
+        stat[(w * R + h) * 2] = m[r];
+        stat[(w * R + h) * 2 + 1] = lt;
+      }
+    }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < R * kHeadDim; idx += 64 * kFlashWaves) {
+    const int h = idx / kHeadDim, d = idx % kHeadDim;
+    float M = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kFlashWaves; ++i) M = fmaxf(M, stat[(i * R + h) * 2]);
+    float den = 0.0f, num = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kFlashWaves; ++i) {
+      const float e = expf(stat[(i * R + h) * 2] - M);  // a wave without positions: exp(-inf) = 0
+      den = fmaf(e, stat[(i * R + h) * 2 + 1], den);
+      num = fmaf(e, osum[(i * R + h) * kHeadDim + d], num);
+    }
+    float* wp = ws + ((int64_t)(g * R + h) * T + split) * (kHeadDim + 2);
+    wp[2 + d] = num;
+    if (d == 0) {
+      wp[0] = M;
+      wp[1] = den;
+    }
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(64 * kFlashWaves) void attn_qkv_flash_kernel(
+    uint16_t* __restrict__ kc, uint16_t* __restrict__ vc, int S_max, int pos, const uint16_t* __restrict__ qkv,
+    const uint16_t* __restrict__ qw, const float* __restrict__ cs, float eps, int Hq, int chunk,
+    const uint16_t* __restrict__ kw, int Hkv, int T, float* __restrict__ ws) {
+  flash_block<R>(kc, vc, S_max, pos, qkv, qw, cs, eps, Hq, chunk, kw, Hkv, T, ws);
+}
+
 // Combines the T partials of one query head (block h of NW waves): every wave
 // forms the maximum M of the tiles' maxima and the denominator sum_t l_t
 // exp(m_t - M) itself (the same fixed order in every wave); wave w adds
@@ -591,6 +875,16 @@ int attention_qkv_tile(int64_t Hkv, int64_t L) {
   return work >= 32768 ? 64 : work >= 4096 ? 32 : 16;
 }
 
+// Whether the long-context kernel takes the call.  Its fixed part (about 8 us:
+// two launches, one step of every wave, the joining of eight waves) is longer
+// than the tile kernel's, its slope less than half.  Measured on MI355X, Hq:Hkv at
+// L, tile kernel -> this one: 32:8 at 8192 14.5 -> 14.9 us, 12288 19.5 -> 19.4,
+// 16384 25.7 -> 22.1, 32768 46.1 -> 34.1; 64:8 at 32768 50.6 -> 36.2; 8:8 at 12288
+// 20.5 -> 18.8; with few key/value heads the tile kernel's many records per
+// head cost it more: 4:2 at 8192 12.9 -> 11.7, 8:1 12.4 -> 11.6 and at
+// 32768 23.3 -> 15.9.
+bool long_context(int64_t Hkv, int64_t pos) { return pos >= (Hkv <= 2 ? 8192 : 12288); }
+
 int64_t decode_attention_qkv_tiles(int64_t Hkv, int64_t L) {
   const int P = attention_qkv_tile(Hkv, L);
   return (L + P - 1) / P;
@@ -601,14 +895,34 @@ hipError_t launch_decode_attention_qkv(const uint16_t* qkv, const uint16_t* qw, 
                                        uint16_t* kc, uint16_t* vc, int64_t S_max, uint16_t* out, float* ws,
                                        hipStream_t stream, const LaunchEvents& ev) {
   const int64_t L = pos + 1;
-  const int P = attention_qkv_tile(Hkv, L);
-  const int T = (int)((L + P - 1) / P);
-  const int R = (int)(Hq / Hkv);
   LaunchEvents e1, e2;  // the measurement hook spans both kernels
   e1.start = ev.start;
   e2.stop = ev.stop;
-  const dim3 grid((unsigned)Hkv, (unsigned)T);
+  const int R = (int)(Hq / Hkv);
   const float* cs = cos_sin + pos * kHeadDim;
+  if (long_context(Hkv, pos)) {
+    // About one block per compute unit, its waves taking the same number of steps.
+    const int64_t blocks = std::max<int64_t>(1, 256 / Hkv);  // per key/value head
+    const int64_t unit = kFlashWaves * kFlashStep;
+    const int chunk = (int)((pos + unit * blocks - 1) / (unit * blocks) * unit);
+    const int T = (int)((pos + chunk - 1) / chunk);
+    const dim3 grid((unsigned)Hkv, (unsigned)T);
+#define LAQ_FLASH(RV)                                                                                               \
+  launch(attn_qkv_flash_kernel<RV>, grid, dim3(64 * kFlashWaves), kFlashLds, stream, e1, kc, vc, (int)S_max, (int)pos, \
+         qkv, qw, cs, eps, (int)Hq, chunk, kw, (int)Hkv, T, ws)
+    switch (R) {
+      case 1: LAQ_FLASH(1); break;
+      case 2: LAQ_FLASH(2); break;
+      case 4: LAQ_FLASH(4); break;
+      default: LAQ_FLASH(8); break;
+    }
+#undef LAQ_FLASH
+    launch(attn_combine2_kernel<4>, dim3((unsigned)Hq), dim3(256), 0, stream, e2, (const float*)ws, T, out);
+    return hipGetLastError();
+  }
+  const int P = attention_qkv_tile(Hkv, L);
+  const int T = (int)((L + P - 1) / P);
+  const dim3 grid((unsigned)Hkv, (unsigned)T);
 #define LAQ_ATTN_QKV(RV, PV)                                                                                 \
   launch(attn_qkv_partial_kernel<RV, PV>, grid, dim3(64 * RV), 0, stream, e1, kc, vc, (int)S_max, (int)pos, qkv, \
          qw, cs, eps, (int)Hq, kw, (int)Hkv, T, ws)

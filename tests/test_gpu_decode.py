@@ -133,6 +133,46 @@ def test_decode_attention_qkv(Hq, Hkv, pos, S):
     assert np.array_equal(kc.cpu().numpy(), kh) and np.array_equal(vc.cpu().numpy(), vh)
 
 
+@pytest.mark.parametrize("Hq,Hkv,pos,S", [(32, 8, 12288, 12300), (4, 4, 13055, 13056), (4, 4, 12543, 12600),
+                                           (64, 8, 12801, 12802), (2, 1, 8192, 8200), (8, 1, 8225, 8400),
+                                           (2, 2, 8448, 8449), (1, 1, 20000, 20001), (16, 4, 16383, 16384)])
+def test_decode_attention_qkv_long(Hq, Hkv, pos, S):
+    """The long-context kernel (from position 12288, or 8192 with at most two
+    key/value heads): chunk and step edges (pos a multiple of 32 and 256, one
+    below and one past it, a last chunk with one position and waves with no
+    step), 1 to 8 query heads per key/value head, against the oracle; rows past
+    pos hold NaN and must not be read; rows other than pos stay untouched; the
+    call is deterministic.  A large score late in the context moves the
+    running maximum after most steps."""
+    say("decode_attention_qkv long", Hq, Hkv, pos, S)
+    rng = np.random.default_rng(Hq * 1000 + pos)
+    qkv = f16(rng, (Hq + 2 * Hkv) * 128, 2.0)
+    qw = (1 + 0.2 * rng.standard_normal(128)).astype(np.float16)
+    kw = (1 + 0.2 * rng.standard_normal(128)).astype(np.float16)
+    Kc = f16(rng, (Hkv, S, 128))
+    Vc = f16(rng, (Hkv, S, 128))
+    q_ref, k_ref, v_ref = OD.qk_norm_rope(qkv, qw, kw, pos, Hq, Hkv, 128, EPS, THETA)
+    Kc[:, pos - 5] = (0.5 * q_ref[::Hq // Hkv]).astype(np.float16)
+    Kc[:, pos + 1:] = np.nan
+    Vc[:, pos + 1:] = np.nan
+    kc, vc = dev(Kc), dev(Vc)
+    args = (dev(qkv), dev(qw), dev(kw), dev(cos_sin_table(S)), pos, Hq, Hkv, EPS, kc, vc)
+    out = laq.decode_attention_qkv(*args)
+    torch.cuda.synchronize()
+    kh, vh = kc.cpu().numpy(), vc.cpu().numpy()
+    assert linear_check(kh[:, pos], k_ref)["ok"]
+    assert np.array_equal(vh[:, pos], v_ref.astype(np.float16))
+    others = np.arange(S) != pos
+    assert np.array_equal(kh[:, others].view(np.uint16), Kc[:, others].view(np.uint16))
+    assert np.array_equal(vh[:, others].view(np.uint16), Vc[:, others].view(np.uint16))
+    ref = OD.decode_attention(q_ref.astype(np.float16), kh[:, :pos + 1], vh[:, :pos + 1])
+    r = linear_check(out.cpu().numpy(), ref)
+    assert r["ok"], r
+    out2 = laq.decode_attention_qkv(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+
+
 @pytest.mark.parametrize("M,I", [(1, 9728), (2, 100), (1, 25600)])
 def test_silu_mul(M, I):
     say("silu_mul", M, I)
