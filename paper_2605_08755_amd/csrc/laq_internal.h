@@ -134,16 +134,19 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
 // Skinny GEMM with the activations held in registers (linear_stream.hip), for
 // rows of at most 16 quads: activation rows staged (MT), groups of a quad
 // staged at a time (PH), ring stages (D), partial buffers (nb), tiles per
-// block and step (TS), waves and blocks.  W == 0: the shape is not taken.
+// block and step (TS), quads of a block (nq), waves, blocks per K range and
+// K ranges.  W == 0: the shape is not taken.
 struct StreamPlan {
-  int MT = 0, PH = 0, D = 0, nb = 0, TS = 0, W = 0, nblocks = 0;
+  int MT = 0, PH = 0, D = 0, nb = 0, TS = 0, nq = 0, W = 0, nblocks = 0, ranges = 0;
   uint32_t lds = 0;
 };
-StreamPlan stream_plan(int bits, int M, int64_t N, int G);
+StreamPlan stream_plan(int bits, int M, int64_t N, int G, int ranges);
+// part: null, or device memory for the K ranges' fp32 sums [ranges][M][N]
+// (then y is not written).
 template <int BITS>
 hipError_t launch_linear_stream(const StreamPlan& p, const uint16_t* x, const uint32_t* qweight,
-                                const uint16_t* scales, const uint8_t* zeros, uint16_t* y, int M, int64_t N, int G,
-                                hipStream_t stream, const LaunchEvents& ev);
+                                const uint16_t* scales, const uint8_t* zeros, uint16_t* y, float* part, int M,
+                                int64_t N, int G, hipStream_t stream, const LaunchEvents& ev);
 
 // calls[i].{x, qw, scales, zeros, y, N, G} filled in by the caller; count in 1..kMaxGroup.
 template <int BITS>

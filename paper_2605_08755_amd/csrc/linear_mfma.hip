@@ -143,7 +143,18 @@ __host__ __device__ constexpr int mfma_block_waves(int M, int nq) {
   return wmax < nq ? wmax : nq;
 }
 
-template <int BITS, int TW>
+// The same with the codes through LDS (request_quad), a unit per wave beside
+// its slab: as many waves as fit, at most 16, and half the quads where two
+// rounds take them.  (Measured on MI355X, 19 quads: M = 8 10 waves 7.71 us, 13
+// waves 8.10; M = 16, three rounds, 8 waves 8.97, 7 waves 9.90.)
+__host__ __device__ constexpr int mfma_codes_waves(int bits, int M, int nq) {
+  const int fit = kBlockLdsU4 * 16 / (M * 1024 + unit_bytes(bits));
+  const int wmax = fit < 16 ? fit : 16;
+  const int rounds = (nq + wmax - 1) / wmax;
+  return rounds == 2 ? (nq + 1) / 2 : (wmax < nq ? wmax : nq);
+}
+
+template <int BITS, int TW, bool CLDS>
 __device__ __forceinline__ void mfma_block(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ qw, const uint16_t* __restrict__ scales,
     const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, int M, int N, int G, int block, int W) {
@@ -187,8 +198,11 @@ __device__ __forceinline__ void mfma_block(
     const uint32_t dead = (uint32_t)(gq >= G) << 31;
     u32x4 wv[TW][BITS];
     uint32_t sraw[TW], zraw[TW];
+    char* const unit = reinterpret_cast<char*>(wslabs) + W * M * 1024 + wave * unit_bytes(BITS);
+    static_assert(!CLDS || TW == 1, "one unit per wave");
+    if constexpr (CLDS) request_quad<BITS, kWeightPolicy>(unit, qr, sr, zr, lane, Q, G, true);
 #pragma unroll
-    for (int t = 0; t < TW; ++t) {
+    for (int t = 0; t < (CLDS ? 0 : TW); ++t) {
       const int nrow = 16 * t + nl;
 #pragma unroll
       for (int p = 0; p < BITS; ++p)
@@ -212,8 +226,19 @@ __device__ __forceinline__ void mfma_block(
     //    component j) and the four groups' scale | zero << 16 in every quarter.
     uint32_t wt[TW][BITS][4];
     uint32_t szj[TW][4];
+    if constexpr (CLDS) {
+      uint32_t cw[4][BITS];
+      u32x4 sc, zc;
+      read_quad<BITS>(cw, sc, zc, lds_byte(unit), lane);
 #pragma unroll
-    for (int t = 0; t < TW; ++t) {
+      for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int p = 0; p < BITS; ++p) wt[0][p][j] = cw[j][p];
+        szj[0][j] = sc[j] | zc[j] << 16;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < (CLDS ? 0 : TW); ++t) {
 #pragma unroll
       for (int p = 0; p < BITS; ++p) {
         wt[t][p][0] = wv[t][p][0];
@@ -645,13 +670,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     if (i0 + e < MN) y[i0 + e] = __builtin_bit_cast(uint16_t, (_Float16)acc[e]);
 }
 
-template <int BITS, int TW>
+template <int BITS, int TW, bool CLDS>
 __global__ __launch_bounds__(1024 / TW) void linear_mfma_kernel(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ qw, const uint16_t* __restrict__ scales,
     const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, int M, int N, int G, int nblocks) {
   const int block = xcd_block(nblocks);
   if (block >= nblocks) return;  // idle slot of the XCD-rounded grid
-  mfma_block<BITS, TW>(x, qw, scales, zeros, y, M, N, G, block, mfma_block_waves(M, (G + 3) >> 2));
+  const int nq = (G + 3) >> 2;
+  mfma_block<BITS, TW, CLDS>(x, qw, scales, zeros, y, M, N, G, block,
+                             CLDS ? mfma_codes_waves(BITS, M, nq) : mfma_block_waves(M, nq));
 }
 
 // Several independent calls in one launch (one 16-row tile per block); the
@@ -664,7 +691,7 @@ __global__ __launch_bounds__(1024) void linear_mfma_group_kernel(const LinearGro
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
     if (j < grp.count && b >= grp.call[j].first_block) c = grp.call[j];
-  mfma_block<BITS, 1>(c.x, c.qw, c.scales, c.zeros, c.y, M, c.N, c.G, b - c.first_block, grp.waves);
+  mfma_block<BITS, 1, false>(c.x, c.qw, c.scales, c.zeros, c.y, M, c.N, c.G, b - c.first_block, grp.waves);
 }
 
 // ---------------------------------------------------------------------------
@@ -1017,6 +1044,9 @@ bool stream_pays(int M, int64_t tiles, int nq) {
   return units >= (nq >= 8 ? 12288 : 16384);
 }
 
+constexpr int64_t kStreamSplitMinUnits = 2048;
+constexpr int kStreamSplitMaxRanges = 16;  // at least 16 blocks per range
+
 template <int BITS>
 hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const uint16_t* scales,
                               const uint8_t* zeros, uint16_t* y, int M, int64_t N, int64_t K,
@@ -1026,8 +1056,8 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
   const int nq = (G + 3) / 4;
   const int64_t tiles = (N + 15) / 16;
   if (stream_pays(M, tiles, nq))
-    if (const StreamPlan st = stream_plan(BITS, M, N, G); st.W > 0)
-      return launch_linear_stream<BITS>(st, x, qweight, scales, zeros, y, M, N, G, stream, ev);
+    if (const StreamPlan st = stream_plan(BITS, M, N, G, 1); st.W > 0)
+      return launch_linear_stream<BITS>(st, x, qweight, scales, zeros, y, nullptr, M, N, G, stream, ev);
   // Many tiles, rows of at most five quads, M > 4 (W4: M > 8; at M <= 8 the
   // one-tile blocks below are faster for W4): three tiles per block share
   // the quads' slabs, one wave per (tile, quad).
@@ -1097,10 +1127,28 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
   // ranges' partial sums in order.
   const SplitPlan sp = mfma_split_plan(M, N, G);
   if (sp.S > 1 && workspace && workspace_bytes >= split_workspace_bytes(sp, M, N)) {
-    const int nblocks = sp.tile_blocks * sp.S;
+    const int64_t MN = (int64_t)M * N;
+    const dim3 rgrid((unsigned)((MN + 1023) / 1024));
     LaunchEvents e1, e2;  // the measurement hook spans both kernels
     e1.start = ev.start;
     e2.stop = ev.stop;
+    // Enough (tile, quad) units: ranges of up to 16 quads in the streaming
+    // kernel (fewer ranges than below, so they fit the same workspace).
+    // Measured on MI355X, both kernels of the split: 5120 x 25600 at M = 3 / 8 / 16
+    // 27.1 / 28.3 / 29.9 -> 18.7 / 21.4 / 19.8 us, 8192 x 20480 at M = 8 34.0 ->
+    // 26.2, 1024 x 25600 (3200 units) at M = 4 11.2 -> 8.9.
+    const int ranges = (nq + 15) / 16;
+    const StreamPlan st = tiles * nq >= kStreamSplitMinUnits && ranges <= kStreamSplitMaxRanges
+                              ? stream_plan(BITS, M, N, G, ranges)
+                              : StreamPlan{};
+    if (st.W > 0 && st.ranges <= sp.S) {
+      const hipError_t e =
+          launch_linear_stream<BITS>(st, x, qweight, scales, zeros, nullptr, workspace, M, N, G, stream, e1);
+      if (e != hipSuccess) return e;
+      launch(splitk_reduce_kernel, rgrid, dim3(256), 0, stream, e2, (const float*)workspace, y, st.ranges, MN);
+      return hipGetLastError();
+    }
+    const int nblocks = sp.tile_blocks * sp.S;
     const dim3 grid(xcd_grid(nblocks)), blk(64 * kFullTiles);
     const uint32_t lds = (uint32_t)sp.qs * kSlabBytes;
     switch (sp.qs) {
@@ -1110,9 +1158,19 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
       case 4: launch(linear_mfma_split_kernel<BITS, 4>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
       default: launch(linear_mfma_split_kernel<BITS, 5>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
     }
-    const int64_t MN = (int64_t)M * N;
-    launch(splitk_reduce_kernel, dim3((unsigned)((MN + 1023) / 1024)), dim3(256), 0, stream, e2,
-           (const float*)workspace, y, sp.S, MN);
+    launch(splitk_reduce_kernel, rgrid, dim3(256), 0, stream, e2, (const float*)workspace, y, sp.S, MN);
+    return hipGetLastError();
+  }
+  // Codes through LDS, one tile per block, while the blocks that fit on the
+  // compute units hold every tile at once (measured on MI355X, M = 4 / 16:
+  // 4096 x 16384 18.4 / 23.6 -> 10.2 / 13.9 us, against two tiles per block on half
+  // the compute units; 1024 x 8192 5.8 / 7.6 -> 5.0 / 6.0; 2560 x 9728 7.2 / 9.6 ->
+  // 7.1 / 9.0).
+  const int Wc = mfma_codes_waves(BITS, M, nq);
+  const size_t lds_codes = (size_t)Wc * (M * 1024 + unit_bytes(BITS));
+  if (tiles <= 256 * (int64_t)((size_t)kBlockLdsU4 * 16 / lds_codes)) {
+    launch(linear_mfma_kernel<BITS, 1, true>, dim3(xcd_grid(tiles)), dim3(64 * Wc), (uint32_t)lds_codes, stream, ev, x,
+           qweight, scales, zeros, y, M, (int)N, G, (int)tiles);
     return hipGetLastError();
   }
   // Two tiles per block share each activation fragment when rows are long
@@ -1125,11 +1183,11 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
   const unsigned blocks = xcd_grid(nblocks);
   const uint32_t lds = (uint32_t)W * M * kSlabRowU4 * 16;
   if (TW == 2)
-    launch(linear_mfma_kernel<BITS, 2>, dim3(blocks), dim3(64 * W), lds, stream, ev, x, qweight, scales, zeros, y, M,
+    launch(linear_mfma_kernel<BITS, 2, false>, dim3(blocks), dim3(64 * W), lds, stream, ev, x, qweight, scales, zeros, y, M,
            (int)N, G, nblocks);
   else
-    launch(linear_mfma_kernel<BITS, 1>, dim3(blocks), dim3(64 * W), lds, stream, ev, x, qweight, scales, zeros, y, M,
-           (int)N, G, nblocks);
+    launch(linear_mfma_kernel<BITS, 1, false>, dim3(blocks), dim3(64 * W), lds, stream, ev, x, qweight, scales, zeros, y,
+           M, (int)N, G, nblocks);
   return hipGetLastError();
 }
 

@@ -202,16 +202,23 @@ __device__ __forceinline__ void wait_stages(int later) {
   else wait_vmcnt<3 * WL>();
   __builtin_amdgcn_sched_barrier(0);
 }
+// TS tiles per step, nb partial buffers (2: one barrier per step, 1: two), D
+// ring stages, nq quads, and whether the sums are those of a K range.
+constexpr int stream_cfg(int TS, int nb, int D, int nq, bool partial) {
+  return TS | nb << 5 | D << 7 | nq << 10 | (int)partial << 15;
+}
 constexpr int kStreamStages = 4;  // most stages of the ring
 
 // MT: activation rows staged (4, 8 or 16; rows past M read zeros).
 // PH: groups of a quad staged at a time (4, or 2 or 1 where the waves' slabs of
-// four groups do not fit in LDS).  cfg: TS | nb << 8 | D << 16, nb the partial
-// buffers (2: one barrier per tile, 1: two), D the stages of the ring.
+// four groups do not fit in LDS).  cfg: stream_cfg().  The block's quads are
+// q0 .. q0 + nq - 1 (those past the row read zeros); a range of them writes its
+// fp32 partial sums to part [M][N] instead of the fp16 outputs to y.
 template <int BITS, int MT, int PH>
 __device__ __forceinline__ void stream_block(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ qw, const uint16_t* __restrict__ scales,
-    const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, int M, int N, int G, int cfg, int b, int nblocks) {
+    const uint8_t* __restrict__ zeros, uint16_t* __restrict__ y, float* __restrict__ part, int M, int N, int G,
+    int cfg, int b, int nblocks, int q0) {
   typedef __attribute__((address_space(3))) void lds_void;
   extern __shared__ u32x4 lds[];
   constexpr int SB = unit_bytes(BITS);
@@ -221,13 +228,13 @@ __device__ __forceinline__ void stream_block(
   constexpr int WL = BITS + 2;  // loads of a stage per wave
   constexpr int XR = PH * 16;   // 16-byte pieces of a slab row
 
-  const int nq = (G + 3) >> 2;
-  const int TS = cfg & 0xFF, nb = (cfg >> 8) & 0xFF, D = cfg >> 16;
+  const int TS = cfg & 31, nb = (cfg >> 5) & 3, D = (cfg >> 7) & 7, nq = (cfg >> 10) & 31;
+  const bool partial = cfg >> 15;
   const int W = TS * nq;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int t = TS == 1 ? 0 : w / nq;  // tile of the group
-  const int q = w - t * nq;            // quad of the row
+  const int q = w - t * nq;            // quad of the block's
   const int K = 128 * G;
   char* const ldsb = reinterpret_cast<char*>(lds);
 
@@ -241,7 +248,7 @@ __device__ __forceinline__ void stream_block(
     constexpr int RPI = 4 / PH;  // slab rows per load instruction
     for (int i = t; i < MT / RPI; i += TS) {
       const int m = i * RPI + lane / XR;
-      const int col = 512 * q + 128 * PH * ph + 8 * ((lane % XR) ^ (m & 7));
+      const int col = 512 * (q0 + q) + 128 * PH * ph + 8 * ((lane % XR) ^ (m & 7));
       __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void*)(slab + i * 1024), 16,
                                                (uint32_t)(m * K + col) * 2 | (uint32_t)!(m < M && col < K) << 31, 0,
                                                0, 0);
@@ -266,7 +273,7 @@ __device__ __forceinline__ void stream_block(
   const bool whole = (G & 7) == 0;    // rows of whole lines
   const int h = paired ? q & 1 : 0;
   const int lr = paired ? 8 * h + (lane >> 3) : lane >> 2;
-  const int gb = paired ? 4 * (q - h) : 4 * q;  // first group loaded
+  const int gb = 4 * (q0 + q - h);  // first group loaded
   const int gc = gb + (paired ? (lane & 7) ^ ((lr >> 1) & 7) : (lane & 3) ^ ((lr >> 2) & 3));
   const int gz = gb + (paired ? lane & 7 : lane & 3);
   uint32_t wo[BITS];
@@ -395,11 +402,14 @@ __device__ __forceinline__ void stream_block(
     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xsum, sown * (float)zo_ * -0x1p-24f, acc, 0, 0, 0);
 
     const uint32_t pbuf = parts + (uint32_t)(((nb - 1) & i) * W * PB);
+    // (The products by 2^24 also stand between the matrix instruction and the
+    // stores: the compiler inserts the wait states that a reader of its result
+    // needs before instructions it knows, not before inline assembly.)
     if (LV == 64 || lane < LV) {
       const uint32_t pa = pbuf + w * PB + lane * 4;
       static_for<NR>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
-        lds_write_b32<r * LV * 4>(pa, __builtin_bit_cast(uint32_t, (float)acc[r]));
+        lds_write_b32<r * LV * 4>(pa, __builtin_bit_cast(uint32_t, acc[r] * 0x1p24f));
       });
     }
     // The next iteration's stage has landed when only later stages' loads
@@ -423,7 +433,10 @@ __device__ __forceinline__ void stream_block(
       }
       const int m = 4 * (ln >> 4) + r;
       const int64_t n = ((int64_t)(b + i * nblocks) * TS + tt) * 16 + (ln & 15);
-      if (m < M && n < N) y[(int64_t)m * N + n] = __builtin_bit_cast(uint16_t, (_Float16)(v * 0x1p24f));
+      if (m < M && n < N) {
+        if (partial) part[(int64_t)m * N + n] = v;
+        else y[(int64_t)m * N + n] = __builtin_bit_cast(uint16_t, (_Float16)v);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (i + D < iters) issue(i + D, S);
@@ -432,21 +445,28 @@ __device__ __forceinline__ void stream_block(
   }
 }
 
+// part: K ranges of nq quads, block b taking range b / nblocks and writing
+// part[range][M][N]; or null (one range, outputs to y).
 template <int BITS, int MT, int PH>
 __global__ __launch_bounds__(64 * kStreamWaves) void linear_stream_kernel(
     const uint16_t* __restrict__ x, const uint32_t* __restrict__ qw, const uint16_t* __restrict__ scales,
-    const uint8_t* __restrict__ zeros, int M, int N, int G, int cfg, int nblocks, uint16_t* __restrict__ y) {
-  stream_block<BITS, MT, PH>(x, qw, scales, zeros, y, M, N, G, cfg, (int)blockIdx.x, nblocks);
+    const uint8_t* __restrict__ zeros, int M, int N, int G, int cfg, int nblocks, uint16_t* __restrict__ y,
+    float* __restrict__ part) {
+  const int range = cfg >> 15 ? (int)blockIdx.x / nblocks : 0;
+  stream_block<BITS, MT, PH>(x, qw, scales, zeros, y, part + (int64_t)range * M * N, M, N, G, cfg,
+                             (int)blockIdx.x - range * nblocks, nblocks, range * ((cfg >> 10) & 31));
 }
 
 }  // namespace
 
-StreamPlan stream_plan(int bits, int M, int64_t N, int G) {
+StreamPlan stream_plan(int bits, int M, int64_t N, int G, int ranges) {
   StreamPlan p;
-  const int nq = (G + 3) / 4;
+  // (ranges of an even number of quads, so that whole lines stay in one range)
+  const int nq_all = (G + 3) / 4;
+  const int nq = ranges == 1 ? nq_all : ((nq_all + ranges - 1) / ranges + 1) / 2 * 2;
   if (nq > kStreamWaves) return p;
   const int64_t tiles = (N + 15) / 16;
-  const int MT = M <= 1 ? 1 : M <= 2 ? 2 : M <= 4 ? 4 : M <= 8 ? 8 : 16;
+  const int MT = M <= 4 ? 4 : M <= 8 ? 8 : 16;
   const int SB = unit_bytes(bits), PB = partial_bytes(MT);
   auto lds = [&](int TS, int PH, int D, int nb) {
     const int W = TS * nq;
@@ -460,7 +480,7 @@ StreamPlan stream_plan(int bits, int M, int64_t N, int G) {
   while (PH > 1 && lds(TS, PH, 2, 1) > kStreamLdsBytes) PH /= 2;
   if (lds(TS, PH, 2, 1) > kStreamLdsBytes) return p;
   const int64_t groups = (tiles + TS - 1) / TS;
-  const int nblocks = (int)std::min<int64_t>(groups, 256);
+  const int nblocks = (int)std::min<int64_t>(groups, 256 / ranges);
   const int64_t iters = (groups + nblocks - 1) / nblocks;
   p.D = 1;
   while (p.D < kStreamStages && p.D < iters && lds(TS, PH, p.D + 1, 1) <= kStreamLdsBytes) ++p.D;
@@ -470,33 +490,36 @@ StreamPlan stream_plan(int bits, int M, int64_t N, int G) {
   p.TS = TS;
   p.W = TS * nq;
   p.nblocks = nblocks;
+  p.nq = nq;
+  p.ranges = (nq_all + nq - 1) / nq;
   p.lds = (uint32_t)lds(TS, PH, p.D, p.nb);
   return p;
 }
 
 template <int BITS>
 hipError_t launch_linear_stream(const StreamPlan& p, const uint16_t* x, const uint32_t* qweight,
-                                const uint16_t* scales, const uint8_t* zeros, uint16_t* y, int M, int64_t N, int G,
-                                hipStream_t stream, const LaunchEvents& ev) {
-#define LAQ_ST_D(MTV, PHV)                                                                                    \
-  launch(linear_stream_kernel<BITS, MTV, PHV>, dim3(p.nblocks), dim3(64 * p.W), p.lds, stream, ev, x, qweight, \
-         scales, zeros, M, (int)N, G, p.TS | p.nb << 8 | p.D << 16, p.nblocks, y)
-  if (p.MT == 16 && p.PH == 4) LAQ_ST_D(16, 4);
-  else if (p.MT == 16 && p.PH == 2) LAQ_ST_D(16, 2);
-  else if (p.MT == 16 && p.PH == 1) LAQ_ST_D(16, 1);
-  else if (p.MT == 8 && p.PH == 4) LAQ_ST_D(8, 4);
-  else if (p.MT == 8 && p.PH == 2) LAQ_ST_D(8, 2);
-  else if (p.MT == 4 && p.PH == 4) LAQ_ST_D(4, 4);
+                                const uint16_t* scales, const uint8_t* zeros, uint16_t* y, float* part, int M,
+                                int64_t N, int G, hipStream_t stream, const LaunchEvents& ev) {
+  const int cfg = stream_cfg(p.TS, p.nb, p.D, p.nq, part != nullptr);
+#define LAQ_ST(MTV, PHV)                                                                                             \
+  launch(linear_stream_kernel<BITS, MTV, PHV>, dim3(p.nblocks * p.ranges), dim3(64 * p.W), p.lds, stream, ev, x, \
+         qweight, scales, zeros, M, (int)N, G, cfg, p.nblocks, y, part)
+  if (p.MT == 16 && p.PH == 4) LAQ_ST(16, 4);
+  else if (p.MT == 16 && p.PH == 2) LAQ_ST(16, 2);
+  else if (p.MT == 16 && p.PH == 1) LAQ_ST(16, 1);
+  else if (p.MT == 8 && p.PH == 4) LAQ_ST(8, 4);
+  else if (p.MT == 8 && p.PH == 2) LAQ_ST(8, 2);
+  else if (p.MT == 4 && p.PH == 4) LAQ_ST(4, 4);
   else return hipErrorInvalidValue;
-#undef LAQ_ST_D
+#undef LAQ_ST
   return hipGetLastError();
 }
 
 template hipError_t launch_linear_stream<3>(const StreamPlan&, const uint16_t*, const uint32_t*, const uint16_t*,
-                                            const uint8_t*, uint16_t*, int, int64_t, int, hipStream_t,
+                                            const uint8_t*, uint16_t*, float*, int, int64_t, int, hipStream_t,
                                             const LaunchEvents&);
 template hipError_t launch_linear_stream<4>(const StreamPlan&, const uint16_t*, const uint32_t*, const uint16_t*,
-                                            const uint8_t*, uint16_t*, int, int64_t, int, hipStream_t,
+                                            const uint8_t*, uint16_t*, float*, int, int64_t, int, hipStream_t,
                                             const LaunchEvents&);
 
 }  // namespace laq
