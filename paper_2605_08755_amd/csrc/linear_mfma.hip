@@ -144,12 +144,13 @@ __host__ __device__ constexpr int mfma_block_waves(int M, int nq) {
 }
 
 // The same with the codes through LDS (request_quad), a unit per wave beside
-// its slab: as many waves as fit, at most 16, and half the quads where two
-// rounds take them.  (Measured on MI355X, 19 quads: M = 8 10 waves 7.71 us, 13
+// its slab: as many waves as fit, at most 16 (8 at M > 8), and half the quads
+// where two rounds take them.  (Measured on MI355X, 19 quads: M = 8 10 waves 7.71 us, 13
 // waves 8.10; M = 16, three rounds, 8 waves 8.97, 7 waves 9.90.)
 __host__ __device__ constexpr int mfma_codes_waves(int bits, int M, int nq) {
   const int fit = kBlockLdsU4 * 16 / (M * 1024 + unit_bytes(bits));
-  const int wmax = fit < 16 ? fit : 16;
+  const int most = M > 8 ? 8 : 16;
+  const int wmax = fit < most ? fit : most;
   const int rounds = (nq + wmax - 1) / wmax;
   return rounds == 2 ? (nq + 1) / 2 : (wmax < nq ? wmax : nq);
 }
