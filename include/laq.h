@@ -173,10 +173,10 @@ laq_status laq_linear_w3g128(const void *x, const uint32_t *qweight,
  * (fp32 partial sums per K range, added in a fixed order by a second kernel).
  * It applies on the matrix-core path (M >= 2) to rows of at least 40 quads
  * of four groups (K > 19968) and fewer than 1024 tiles of 16 rows
- * (N <= 16368): there, four tiles per workgroup share each activation slab
- * and the K ranges give every compute unit work, which outweighs the second
- * kernel (measured on MI355X: Qwen3-32B down projection, N = 5120,
- * K = 25600, M = 16: 33.2 -> 31.3 us; shorter rows measured slower split).  Returns 0 when the call
+ * (N <= 16368): there, a workgroup reads a range of the activations once for
+ * many tiles and the K ranges give every compute unit work, which outweighs
+ * the second kernel (measured on MI355X: Qwen3-32B down projection, N = 5120,
+ * K = 25600, M = 16: 33.2 us in one piece, 19.8 us split).  Returns 0 when the call
  * never splits K (then the _ws entry point is the plain one), otherwise an
  * upper bound of what the call uses.  Depends on the shape only (not on the
  * bit width); an invalid shape gives 0.
@@ -267,8 +267,7 @@ laq_status laq_linear_swiglu_w3g128(const void *x, const uint32_t *qweight,
  *   M      [in]  activation rows of every call, 1..16.
  *
  * Results: each y equals that call's laq_linear_w3g128 result within the
- * linear tolerance; on the one-row VALU path (M <= 2, and M <= 4 with rows of
- * at most 3072) bit for bit.  One activation row longer than the LDS holds
+ * linear tolerance; on the VALU path (M <= 2) bit for bit.  One activation row longer than the LDS holds
  * (K > ~29000) makes the group one launch per call, with the same results.
  */
 typedef struct laq_linear_call {

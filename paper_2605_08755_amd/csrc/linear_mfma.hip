@@ -16,13 +16,14 @@
 // exactly.  One v_and_or_b32 + one v_pk_add_f16 per two codes.
 //
 // Kernels: one wave per quad of a 16-row tile, every load issued at once
-// (rows of at most ten quads: fewer than 1024 tiles, or M <= 4); the same
+// (rows of at most ten quads: fewer than 1024 tiles, or M <= 8); the same
 // with three tiles per block sharing the quads' slabs (many tiles, rows of at
 // most five quads, M > 4); one or two 16-row tiles per block, its waves
 // splitting the row's quads (fewer tiles, longer rows); four tiles per block
-// over a K range, one quad ahead (split K, whose fp32 partials a second
-// kernel adds in order); four or eight tiles per block walking K one quad at
-// a time, two quads ahead (many tiles, longer rows).  Every reduction order
+// over a K range, one quad ahead (split K with little work, whose fp32 partials
+// a second kernel adds in order); four or eight tiles per block walking K one
+// quad at a time, two quads ahead (many tiles, longer rows).  Calls with many
+// (tile, quad) units go to linear_stream.hip instead.  Every reduction order
 // is fixed, so results are deterministic.
 #include "mfma_util.h"
 
