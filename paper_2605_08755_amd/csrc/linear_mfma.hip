@@ -42,54 +42,6 @@ namespace {
 constexpr int kWeightPolicy = 0;    // plain
 constexpr int kWeightPolicyNT = 2;  // non-temporal
 
-__device__ __forceinline__ uint32_t pk_add_f16(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b));
-}
-
-// fp16 bit patterns of -(2^(10-p) + z) in both halves, for the field
-// offsets used by the layouts (ulp of 2^(10-p) is 2^-p, so + z is + z*2^p
-// ulps).  zz holds z in both 16-bit halves; z << shift < 2^11, so no carry
-// crosses between the halves.
-__device__ __forceinline__ uint32_t neg_magic(uint32_t base_bits, uint32_t zz, uint32_t shift) {
-  return (base_bits | (base_bits << 16)) + (zz << shift);
-}
-
-// Exact (q - z) pairs of one 32-code chunk, in natural order: pair t holds
-// codes 2t (low half) and 2t+1 (high half).
-template <int BITS>
-__device__ __forceinline__ void unpack_chunk_exact(const uint32_t (&w)[BITS], uint32_t z1, uint32_t (&pr)[16]) {
-  const uint32_t z = z1 | (z1 << 16);
-  if constexpr (BITS == 3) {
-    const uint32_t n0 = neg_magic(0xE400u, z, 0);  // -(1024 + z): fields at bits 0-2
-    const uint32_t n3 = neg_magic(0xD800u, z, 3);  // -(128 + z):  bits 3-5
-    const uint32_t n6 = neg_magic(0xCC00u, z, 6);  // -(16 + z):   bits 6-8
-    const uint32_t n7 = neg_magic(0xC800u, z, 7);  // -(8 + z):    bits 7-9
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const uint32_t t = w[p] >> 10;
-      pr[5 * p + 0] = pk_add_f16(and_or(w[p], 0x00070007u, 0x64006400u), n0);
-      pr[5 * p + 1] = pk_add_f16(and_or(w[p], 0x00380038u, 0x58005800u), n3);
-      pr[5 * p + 2] = pk_add_f16(and_or(w[p], 0x01C001C0u, 0x4C004C00u), n6);
-      pr[5 * p + 3] = pk_add_f16(and_or(t, 0x00070007u, 0x64006400u), n0);
-      pr[5 * p + 4] = pk_add_f16(and_or(t, 0x00380038u, 0x58005800u), n3);
-    }
-    // codes 30/31: code bit j is bit 9 / bit 25 of plane j -> field at bits 7-9
-    const uint32_t spare = ((w[0] >> 2) & 0x00800080u) | ((w[1] >> 1) & 0x01000100u) | (w[2] & 0x02000200u);
-    pr[15] = pk_add_f16(spare | 0x48004800u, n7);
-  } else {
-    const uint32_t n0 = neg_magic(0xE400u, z, 0);  // -(1024 + z): nibbles at bits 0-3
-    const uint32_t n4 = neg_magic(0xD400u, z, 4);  // -(64 + z):   bits 4-7
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t t = w[p] >> 8;
-      pr[4 * p + 0] = pk_add_f16(and_or(w[p], 0x000F000Fu, 0x64006400u), n0);
-      pr[4 * p + 1] = pk_add_f16(and_or(w[p], 0x00F000F0u, 0x54005400u), n4);
-      pr[4 * p + 2] = pk_add_f16(and_or(t, 0x000F000Fu, 0x64006400u), n0);
-      pr[4 * p + 3] = pk_add_f16(and_or(t, 0x00F000F0u, 0x54005400u), n4);
-    }
-  }
-}
-
 // Fragment reads from an LDS slab that direct-to-LDS loads fill, written as
 // inline assembly on purpose: the compiler's wait insertion treats any LDS
 // read that follows a direct-to-LDS load as dependent on every such load in

@@ -16,13 +16,15 @@
 //    go memory -> LDS with four lanes per row (direct-to-LDS, no registers)
 //    and LDS -> registers in operand order, which also makes the cross-lane
 //    transposes of a register path unnecessary.
-//  - Vector ALU work per weight.  A code field masked out of its word is an
-//    fp16 subnormal of value q * 2^(p-24), exact as a matrix-core operand, so
-//    a pair of codes costs one v_and_b32 (and a third of a shift), with the
-//    zero point entering once per group as z * sum x.  Fields are brought to
-//    two offsets (class 0 and class C), each with an accumulator of its own:
-//    26 instructions per 32 codes of W3, where forming exact (q - z) pairs
-//    took 45.
+//  - Vector ALU work per weight.  The products are of exact (q - z) values as
+//    normal fp16 numbers (45 instructions per 32 codes of W3, 40 of W4), the
+//    same as in the tile-by-tile kernels.  (Codes masked out of their words
+//    alone, fp16 subnormals q * 2^(p-24), with z * sum x subtracted per group,
+//    take 26 and ran 51200 x 5120 W3 at M = 16 in 28.6 us instead of 32.2, but
+//    the matrix core keeps fewer bits of products with subnormal operands: the
+//    error before the output's rounding was 2.4e-5 of its RMS for N(0, 1)
+//    activations and 1.6e-4 for one-signed ones at K = 25600, against 1e-7, and
+//    an infinite activation gave NaN in every output of its row.)
 //  - Activation traffic.  x is read once per block, not once per tile.
 #include <algorithm>
 
@@ -38,61 +40,8 @@ constexpr int kStreamWaves = 16;  // waves per block: 128 registers each at 4 pe
 // Lanes of a wave that hold valid results (lane (n, j) holds rows 4j..4j+3 of
 // column n), result registers per lane, and bytes of one wave's partials.
 __host__ __device__ constexpr int valid_lanes(int MT) { return MT == 16 ? 64 : MT == 8 ? 32 : 16; }
-__host__ __device__ constexpr int result_regs(int MT) { return MT < 4 ? MT : 4; }
-__host__ __device__ constexpr int partial_bytes(int MT) { return valid_lanes(MT) * result_regs(MT) * 4; }
-
-// Activation pair held by position i of the operand registers: positions 0-7
-// pair up with the class 0 codes, 8-15 with the class C codes, in the order in
-// which code_pairs makes them.
-template <int BITS>
-__device__ constexpr int pair_at(int i) {
-  constexpr int p3[16] = {0, 3, 2, 5, 8, 7, 10, 13, 1, 4, 6, 9, 11, 14, 12, 15};
-  constexpr int p4[16] = {0, 2, 4, 6, 8, 10, 12, 14, 1, 3, 5, 7, 9, 11, 13, 15};
-  return BITS == 3 ? p3[i] : p4[i];
-}
-
-// The 16 code pairs of a 32-code chunk as fp16 subnormals: b[0..7] of value
-// q * 2^-24 (fields at bits 0-2, or 0-3), b[8..15] of value q * 2^(C-24)
-// (fields at bits 3-5: C = 3, or 4-7: C = 4).
-template <int BITS>
-__device__ __forceinline__ void code_pairs(const uint32_t (&w)[BITS], uint32_t (&b)[16]) {
-  if constexpr (BITS == 3) {
-    constexpr uint32_t m0 = 0x00070007u, m3 = 0x00380038u;
-    const uint32_t t0 = w[0] >> 10, t1 = w[1] >> 10, t2 = w[2] >> 10;
-    const uint32_t u0 = w[0] >> 6, u1 = w[1] >> 6, u2 = w[2] >> 3;
-    b[0] = w[0] & m0;
-    b[1] = t0 & m0;
-    b[2] = u0 & m0;
-    b[3] = w[1] & m0;
-    b[4] = t1 & m0;
-    b[5] = u1 & m0;
-    b[6] = w[2] & m0;
-    b[7] = t2 & m0;
-    b[8] = w[0] & m3;
-    b[9] = t0 & m3;
-    b[10] = w[1] & m3;
-    b[11] = t1 & m3;
-    b[12] = w[2] & m3;
-    b[13] = t2 & m3;
-    b[14] = u2 & m3;
-    // codes 30/31: code bit j is bit 9 / bit 25 of plane j -> field at bits 3-5
-    b[15] = and_or(w[2] >> 4, 0x00200020u, and_or(w[1] >> 5, 0x00100010u, u0 & 0x00080008u));
-  } else {
-    constexpr uint32_t m0 = 0x000F000Fu, m4 = 0x00F000F0u;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t t = w[p] >> 8;
-      b[2 * p + 0] = w[p] & m0;
-      b[2 * p + 1] = t & m0;
-      b[8 + 2 * p + 0] = w[p] & m4;
-      b[8 + 2 * p + 1] = t & m4;
-    }
-  }
-}
-template <int BITS>
-constexpr float kClassRatio = BITS == 3 ? 0.125f : 0.0625f;  // 2^-C
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+constexpr int kResultRegs = 4;
+__host__ __device__ constexpr int partial_bytes(int MT) { return valid_lanes(MT) * kResultRegs * 4; }
 
 // LDS accesses of this kernel are inline assembly: the compiler makes every
 // LDS access that follows a direct-to-LDS load wait for all such loads in
@@ -109,57 +58,6 @@ __device__ __forceinline__ void lds_read4_b128(u32x4 (&f)[4], const uint32_t (&a
       : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "i"(OFF)
       : "memory");
-}
-// A stage's words of this lane (row n, chunk c of each of the four groups, at
-// a[gi] + plane * 1024), row n's four scales (at asc + BITS * 1024), and the
-// scale and zero point of group c (at aown + BITS * 1024, and 256 further).
-// Planes 1024 bytes apart are offsets 0 and 4 of a read2st64.
-template <int BITS>
-__device__ __forceinline__ void lds_read_stage(uint32_t (&w)[4][BITS], u32x4& sc, uint32_t& so, uint32_t& zo,
-                                               const uint32_t (&a)[4], uint32_t asc, uint32_t aown) {
-  u32x2 d0, d1, d2, d3;
-  if constexpr (BITS == 3) {
-    asm volatile(
-        "ds_read2st64_b32 %0, %11 offset0:0 offset1:4\n\t"
-        "ds_read_b32 %4, %11 offset:2048\n\t"
-        "ds_read_b128 %8, %15 offset:3072\n\t"
-        "ds_read2st64_b32 %1, %12 offset0:0 offset1:4\n\t"
-        "ds_read_b32 %5, %12 offset:2048\n\t"
-        "ds_read2st64_b32 %2, %13 offset0:0 offset1:4\n\t"
-        "ds_read_b32 %6, %13 offset:2048\n\t"
-        "ds_read2st64_b32 %3, %14 offset0:0 offset1:4\n\t"
-        "ds_read_b32 %7, %14 offset:2048\n\t"
-        "ds_read_b32 %9, %16 offset:3072\n\t"
-        "ds_read_b32 %10, %16 offset:3328\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(d0), "=&v"(d1), "=&v"(d2), "=&v"(d3), "=&v"(w[0][2]), "=&v"(w[1][2]), "=&v"(w[2][2]),
-          "=&v"(w[3][2]), "=&v"(sc), "=&v"(so), "=&v"(zo)
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(asc), "v"(aown)
-        : "memory");
-  } else {
-    u32x2 e0, e1, e2, e3;
-    asm volatile(
-        "ds_read2st64_b32 %0, %11 offset0:0 offset1:4\n\t"
-        "ds_read2st64_b32 %4, %11 offset0:8 offset1:12\n\t"
-        "ds_read_b128 %8, %15 offset:4096\n\t"
-        "ds_read2st64_b32 %1, %12 offset0:0 offset1:4\n\t"
-        "ds_read2st64_b32 %5, %12 offset0:8 offset1:12\n\t"
-        "ds_read2st64_b32 %2, %13 offset0:0 offset1:4\n\t"
-        "ds_read2st64_b32 %6, %13 offset0:8 offset1:12\n\t"
-        "ds_read2st64_b32 %3, %14 offset0:0 offset1:4\n\t"
-        "ds_read2st64_b32 %7, %14 offset0:8 offset1:12\n\t"
-        "ds_read_b32 %9, %16 offset:4096\n\t"
-        "ds_read_b32 %10, %16 offset:4352\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(d0), "=&v"(d1), "=&v"(d2), "=&v"(d3), "=&v"(e0), "=&v"(e1), "=&v"(e2), "=&v"(e3), "=&v"(sc),
-          "=&v"(so), "=&v"(zo)
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(asc), "v"(aown)
-        : "memory");
-    w[0][2] = e0.x, w[0][3] = e0.y, w[1][2] = e1.x, w[1][3] = e1.y;
-    w[2][2] = e2.x, w[2][3] = e2.y, w[3][2] = e3.x, w[3][3] = e3.y;
-  }
-  w[0][0] = d0.x, w[0][1] = d0.y, w[1][0] = d1.x, w[1][1] = d1.y;
-  w[2][0] = d2.x, w[2][1] = d2.y, w[3][0] = d3.x, w[3][1] = d3.y;
 }
 template <int OFF>
 __device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v) {
@@ -224,7 +122,7 @@ __device__ __forceinline__ void stream_block(
   constexpr int SB = unit_bytes(BITS);
   constexpr int PB = partial_bytes(MT);
   constexpr int LV = valid_lanes(MT);
-  constexpr int NR = result_regs(MT);
+  constexpr int NR = kResultRegs;
   constexpr int WL = BITS + 2;  // loads of a stage per wave
   constexpr int XR = PH * 16;   // 16-byte pieces of a slab row
 
@@ -311,46 +209,15 @@ __device__ __forceinline__ void stream_block(
 #pragma unroll
   for (int jj = 0; jj < 4; ++jj) xa[jj] = lds_byte(slab) + arow * (XR * 16) + 16 * ((4 * j + jj) ^ (arow & 7));
   u32x4 af[4][4];  // [group][matrix-core step]
-  float xs[4];     // this chunk's sum of x per group
   static_for<4 / PH>([&](auto pc) {
     constexpr int ph = decltype(pc)::value;
     if constexpr (ph > 0) fetch_slab(ph);  // this wave's reads of the slab have returned
     wait_stages<WL>(ph == 0 ? 1 : 0);
     if (TS > 1) lds_barrier();  // the other waves' rows of the slab
     static_for<PH>([&](auto gc2) {
-      constexpr int gi = ph * PH + decltype(gc2)::value;
-      u32x4 f[4];
-      lds_read4_b128<256 * decltype(gc2)::value>(f, xa);
-      uint32_t xp[16];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        xp[4 * jj + 0] = f[jj].x;
-        xp[4 * jj + 1] = f[jj].y;
-        xp[4 * jj + 2] = f[jj].z;
-        xp[4 * jj + 3] = f[jj].w;
-      }
-      float s0 = 0.0f, s1 = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        s0 = __builtin_amdgcn_fdot2(as_half2(xp[k]), as_half2(0x3C003C00u), s0, false);
-        s1 = __builtin_amdgcn_fdot2(as_half2(xp[8 + k]), as_half2(0x3C003C00u), s1, false);
-      }
-      xs[gi] = s0 + s1;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        af[gi][k] = u32x4{xp[pair_at<BITS>(4 * k)], xp[pair_at<BITS>(4 * k + 1)], xp[pair_at<BITS>(4 * k + 2)],
-                          xp[pair_at<BITS>(4 * k + 3)]};
+      lds_read4_b128<256 * decltype(gc2)::value>(af[ph * PH + decltype(gc2)::value], xa);
     });
   });
-  // Lane (m, j): the sum of row m over group j (chunks in order).
-  float xsum;
-  {
-    uint32_t r0 = __builtin_bit_cast(uint32_t, xs[0]), r1 = __builtin_bit_cast(uint32_t, xs[1]);
-    uint32_t r2 = __builtin_bit_cast(uint32_t, xs[2]), r3 = __builtin_bit_cast(uint32_t, xs[3]);
-    transpose_quarters(r0, r1, r2, r3);
-    xsum = (__builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1)) +
-           (__builtin_bit_cast(float, r2) + __builtin_bit_cast(float, r3));
-  }
   // The slabs' place becomes ring stages and partials once every wave has
   // read its operands.  (Slabs in LDS of their own, with every stage requested
   // before the activations are used, measured no faster.)
@@ -359,7 +226,7 @@ __device__ __forceinline__ void stream_block(
 
   // 2. Tiles.
   // Where this lane's row nl lies in a stage: the codes of group gi, chunk j,
-  // and the quad's four scales.
+  // and the row's four scales (zero points 256 bytes further).
   uint32_t ca[4], sca;
   {
     const uint32_t st = lds_byte(ldsb + (w - h) * SB) + (paired ? (nl >> 3) * SB : 0);
@@ -374,42 +241,37 @@ __device__ __forceinline__ void stream_block(
   wait_stages<WL>(min(D, iters) - 1);
   lds_barrier();  // (the pair's other half)
   for (int i = 0; i < iters; ++i) {
-    uint32_t cw[4][BITS], so_, zo_;
-    u32x4 sc;
+    uint32_t cw[4][BITS];
+    u32x4 sc, zc;
     {
       const uint32_t off = (uint32_t)(S * W * SB);
       const uint32_t a[4] = {ca[0] + off, ca[1] + off, ca[2] + off, ca[3] + off};
-      lds_read_stage<BITS>(cw, sc, so_, zo_, a, sca + off, sca + off + 4 * j);
+      read_unit<BITS>(cw, sc, zc, a, sca + off);
     }
-    // In units of 2^-24 (the operands' subnormals): sum over the groups of
-    // s * (sum_k q x), then - s z sum x of the four groups by one fp32 MFMA.
     float4_t acc = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int gi = 0; gi < 4; ++gi) {
       uint32_t pr[16];
-      code_pairs<BITS>(cw[gi], pr);
-      float4_t c0 = float4_t{0.f, 0.f, 0.f, 0.f}, c1 = c0;
-      c0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][0]), frag(pr[0], pr[1], pr[2], pr[3]), c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][2]), frag(pr[8], pr[9], pr[10], pr[11]), c1, 0, 0, 0);
-      c0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][1]), frag(pr[4], pr[5], pr[6], pr[7]), c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][3]), frag(pr[12], pr[13], pr[14], pr[15]), c1, 0, 0, 0);
-      const uint32_t scg = gi == 0 ? sc.x : gi == 1 ? sc.y : gi == 2 ? sc.z : sc.w;
-      const _Float16 s = __builtin_bit_cast(_Float16, (uint16_t)(scg & 0xFFFFu));
+      unpack_chunk_exact<BITS>(cw[gi], zc[gi], pr);
+      float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < NR; ++r) acc[r] = fmaf((float)s, fmaf(c1[r], kClassRatio<BITS>, c0[r]), acc[r]);
+      for (int jj = 0; jj < 4; ++jj)
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, af[gi][jj]),
+                                                   frag(pr[4 * jj], pr[4 * jj + 1], pr[4 * jj + 2], pr[4 * jj + 3]), c,
+                                                   0, 0, 0);
+      acc += (float)__builtin_bit_cast(_Float16, (uint16_t)(sc[gi] & 0xFFFFu)) * c;
     }
-    const float sown = (float)__builtin_bit_cast(_Float16, (uint16_t)(so_ & 0xFFFFu));
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xsum, sown * (float)zo_ * -0x1p-24f, acc, 0, 0, 0);
 
     const uint32_t pbuf = parts + (uint32_t)(((nb - 1) & i) * W * PB);
-    // (The products by 2^24 also stand between the matrix instruction and the
+    // (The vector addition above stands between the matrix instruction and the
     // stores: the compiler inserts the wait states that a reader of its result
     // needs before instructions it knows, not before inline assembly.)
     if (LV == 64 || lane < LV) {
       const uint32_t pa = pbuf + w * PB + lane * 4;
       static_for<NR>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
-        lds_write_b32<r * LV * 4>(pa, __builtin_bit_cast(uint32_t, acc[r] * 0x1p24f));
+        const float v = acc[r];  // (a bit cast of the vector's element itself takes element 0)
+        lds_write_b32<r * LV * 4>(pa, __builtin_bit_cast(uint32_t, v));
       });
     }
     // The next iteration's stage has landed when only later stages' loads

@@ -21,11 +21,63 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, uint32_
 // (a & m) | c in one v_and_or_b32.  The mask lives in a scalar register and
 // the magic constant in a vector register (a VOP3 instruction takes no
 // literal on this target, and at most one scalar operand); left to itself the
-// compiler emits a v_and_b32 and a v_or_b32 with literals instead.
+// compiler emits a v_and_b32 and a v_or_b32 with literals instead.  The
+// compiler does not know what the statement is, so it adds no wait states
+// between it and a matrix instruction: its result goes through a packed add
+// before it is an operand, and no register of a matrix result may be free
+// while that result is on its way (every element of it is used afterwards).
 __device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t m, uint32_t c) {
   uint32_t r;
   asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(m), "v"(c));  // mask from a scalar register
   return r;
+}
+
+__device__ __forceinline__ uint32_t pk_add_f16(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b));
+}
+
+// fp16 bit patterns of -(2^(10-p) + z) in both halves, for the field
+// offsets used by the layouts (ulp of 2^(10-p) is 2^-p, so + z is + z*2^p
+// ulps).  zz holds z in both 16-bit halves; z << shift < 2^11, so no carry
+// crosses between the halves.
+__device__ __forceinline__ uint32_t neg_magic(uint32_t base_bits, uint32_t zz, uint32_t shift) {
+  return (base_bits | (base_bits << 16)) + (zz << shift);
+}
+
+// Exact (q - z) pairs of one 32-code chunk, in natural order: pair t holds
+// codes 2t (low half) and 2t+1 (high half).
+template <int BITS>
+__device__ __forceinline__ void unpack_chunk_exact(const uint32_t (&w)[BITS], uint32_t z1, uint32_t (&pr)[16]) {
+  const uint32_t z = z1 | (z1 << 16);
+  if constexpr (BITS == 3) {
+    const uint32_t n0 = neg_magic(0xE400u, z, 0);  // -(1024 + z): fields at bits 0-2
+    const uint32_t n3 = neg_magic(0xD800u, z, 3);  // -(128 + z):  bits 3-5
+    const uint32_t n6 = neg_magic(0xCC00u, z, 6);  // -(16 + z):   bits 6-8
+    const uint32_t n7 = neg_magic(0xC800u, z, 7);  // -(8 + z):    bits 7-9
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint32_t t = w[p] >> 10;
+      pr[5 * p + 0] = pk_add_f16(and_or(w[p], 0x00070007u, 0x64006400u), n0);
+      pr[5 * p + 1] = pk_add_f16(and_or(w[p], 0x00380038u, 0x58005800u), n3);
+      pr[5 * p + 2] = pk_add_f16(and_or(w[p], 0x01C001C0u, 0x4C004C00u), n6);
+      pr[5 * p + 3] = pk_add_f16(and_or(t, 0x00070007u, 0x64006400u), n0);
+      pr[5 * p + 4] = pk_add_f16(and_or(t, 0x00380038u, 0x58005800u), n3);
+    }
+    // codes 30/31: code bit j is bit 9 / bit 25 of plane j -> field at bits 7-9
+    const uint32_t spare = ((w[0] >> 2) & 0x00800080u) | ((w[1] >> 1) & 0x01000100u) | (w[2] & 0x02000200u);
+    pr[15] = pk_add_f16(spare | 0x48004800u, n7);
+  } else {
+    const uint32_t n0 = neg_magic(0xE400u, z, 0);  // -(1024 + z): nibbles at bits 0-3
+    const uint32_t n4 = neg_magic(0xD400u, z, 4);  // -(64 + z):   bits 4-7
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const uint32_t t = w[p] >> 8;
+      pr[4 * p + 0] = pk_add_f16(and_or(w[p], 0x000F000Fu, 0x64006400u), n0);
+      pr[4 * p + 1] = pk_add_f16(and_or(w[p], 0x00F000F0u, 0x54005400u), n4);
+      pr[4 * p + 2] = pk_add_f16(and_or(t, 0x000F000Fu, 0x64006400u), n0);
+      pr[4 * p + 3] = pk_add_f16(and_or(t, 0x00F000F0u, 0x54005400u), n4);
+    }
+  }
 }
 
 __device__ __forceinline__ half8_t frag(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
@@ -101,19 +153,16 @@ __device__ __forceinline__ void request_quad(char* st, __amdgpu_buffer_rsrc_t qr
                                            0, 0, 0);
 }
 
-// This lane's words of the unit at st (row lane % 16, chunk lane / 16 of each
-// of the four groups) and the row's four scales and zero points.  Inline
-// assembly because the compiler makes every LDS read that follows a
-// direct-to-LDS load wait for all such loads in flight; the statement waits
-// for its own reads.
+// This lane's words of a unit (row n, chunk j of each of the four groups, at
+// a[gi] + plane * 1024) and the row's four scales and zero points (at asc +
+// BITS * 1024 and 256 further).  Planes 1024 bytes apart are offsets 0 and 4 of
+// a read2st64.  Inline assembly because the compiler makes every LDS read that
+// follows a direct-to-LDS load wait for all such loads in flight; the statement
+// waits for its own reads.
 template <int BITS>
-__device__ __forceinline__ void read_quad(uint32_t (&w)[4][BITS], u32x4& sc, u32x4& zc, uint32_t st, int lane) {
+__device__ __forceinline__ void read_unit(uint32_t (&w)[4][BITS], u32x4& sc, u32x4& zc, const uint32_t (&a)[4],
+                                          uint32_t asc) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  const uint32_t n = lane & 15;
-  uint32_t a[4];
-#pragma unroll
-  for (uint32_t gi = 0; gi < 4; ++gi) a[gi] = st + n * 64 + 16 * (gi ^ (n >> 2)) + 4 * (lane >> 4);
-  const uint32_t asc = st + n * 16;
   u32x2 d0, d1, d2, d3;
   if constexpr (BITS == 3) {
     asm volatile(
@@ -155,6 +204,16 @@ __device__ __forceinline__ void read_quad(uint32_t (&w)[4][BITS], u32x4& sc, u32
   }
   w[0][0] = d0.x, w[0][1] = d0.y, w[1][0] = d1.x, w[1][1] = d1.y;
   w[2][0] = d2.x, w[2][1] = d2.y, w[3][0] = d3.x, w[3][1] = d3.y;
+}
+
+// The unit at st as request_quad fills it: row lane % 16, chunk lane / 16.
+template <int BITS>
+__device__ __forceinline__ void read_quad(uint32_t (&w)[4][BITS], u32x4& sc, u32x4& zc, uint32_t st, int lane) {
+  const uint32_t n = lane & 15;
+  uint32_t a[4];
+#pragma unroll
+  for (uint32_t gi = 0; gi < 4; ++gi) a[gi] = st + n * 64 + 16 * (gi ^ (n >> 2)) + 4 * (lane >> 4);
+  read_unit<BITS>(w, sc, zc, a, st + n * 16);
 }
 
 }  // namespace

@@ -558,6 +558,78 @@ def test_matrix_core_stream(bits, N, K, Ms):
         assert torch.equal(y, y2) and torch.all(ybuf[M * N:] == 3.0), M
 
 
+# Shapes of the streaming kernel: every count of staged rows and staging phase,
+# split into K ranges, whole and partial lines.
+STREAM_ROUND_SHAPES = [(8200, 8192), (10241, 5120), (26213, 2176), (24581, 4096), (1030, 20608)]
+
+
+def _repeated_rows(bits, N, K, period=251):
+    """Quantized weights whose N rows repeat `period` base rows: (codes, scales,
+    zeros) of the base rows, the base row of each row, and the device tensors."""
+    codes, qw, s, z = oracle_packed(inputs.weights(period, K, cfg=25, layer=bits, proj=K % 97), bits)
+    rows = np.arange(N) % period
+    take = torch.from_numpy(rows).to(DEV)
+    return codes, s, z, rows, [to_dev(a)[take].contiguous() for a in (qw.view(np.int32), s.view(np.float16), z)]
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("N,K", STREAM_ROUND_SHAPES)
+def test_matrix_core_stream_rounding(bits, N, K):
+    """Almost every output is the fp16 rounding of the exact sum itself: what
+    comes before that rounding is a 32-bit accumulation of exact (q - z) x
+    products.  At most K / 32 + K / 128 additions on the way to an output, each
+    off by up to 2^-25 of the sum so far, in random directions: about 1e-6 of
+    the output's RMS for the longest row, and an error e moves a value across a
+    rounding boundary with probability 2 |e| / ulp, where the ulp is 7e-4 of a
+    typical value: 0.2 %.  Bound: 0.5 %.  Activations of both signs, one-signed,
+    subnormal and up to the largest halves.  Rows with the same weights give
+    the same bits wherever they lie."""
+    say("mfma stream rounding", bits, N, K)
+    codes, s, z, rows, (qd, sd, zd) = _repeated_rows(bits, N, K)
+    P = len(codes)
+    for kind, xscale, sscale in (("both signs", 1.0, 1.0), ("one sign", 1.0, 1.0), ("subnormal", 2.0**-17, 2.0**6),
+                                 ("large", 2.0**14, 2.0**-8)):
+        sh = (s.view(np.float16).astype(np.float64) * sscale).astype(np.float16)
+        sk = to_dev(sh)[torch.from_numpy(rows).to(DEV)].contiguous()
+        wrong = total = 0
+        for M in (3, 8, 16):
+            x = inputs.activations(M, K, cfg=25, layer=M).astype(np.float64)
+            x = np.clip((np.abs(x) if kind == "one sign" else x) * xscale, -65504, 65504).astype(np.float16)
+            y = laq.linear(to_dev(x), qd, sk, zd, bits)
+            torch.cuda.synchronize()
+            y = y.cpu().numpy()
+            assert np.array_equal(y, y[:, rows]), (kind, M)
+            ref = oracle.linear(x, codes, sh.view(np.uint16), z)
+            assert np.abs(ref).max() < 60000
+            r = linear_check(y[:, :P], ref)
+            assert r["ok"], (kind, M, r)
+            wrong += int((y[:, :P] != ref.astype(np.float16)).sum())
+            total += ref.size
+        assert wrong <= 0.005 * total, (kind, wrong, total)
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("N,K", [(200, 640), (100, 16384)] + STREAM_ROUND_SHAPES)
+def test_matrix_core_infinite_activation(bits, N, K):
+    """One infinite activation: its row's outputs are infinite with the sign of
+    (q - z) x, or NaN where q = z, on every matrix-core path alike; the other
+    rows' outputs do not change."""
+    say("infinite activation", bits, N, K)
+    codes, s, z, rows, w = _repeated_rows(bits, N, K)
+    d = codes.astype(np.int64) - np.repeat(z.astype(np.int64), 128, axis=1)
+    for M in (3, 8, 16):
+        x = inputs.activations(M, K, cfg=25, layer=M)
+        plain = laq.linear(to_dev(x), *w, bits).cpu().numpy()
+        for row, col, v in ((0, 0, np.inf), (M - 1, K - 1, -np.inf), (1, K // 2 + 5, np.inf)):
+            xi = x.copy()
+            xi[row, col] = v
+            got = laq.linear(to_dev(xi), *w, bits).cpu().numpy()
+            ref = plain.copy()
+            dc = d[rows, col]
+            ref[row] = np.where(dc == 0, np.nan, np.where(dc > 0, v, -v))
+            assert np.array_equal(got, ref, equal_nan=True), (M, row, col)
+
+
 SPLIT_SHAPES = [(5120, 25600), (100, 25088), (3, 20608), (1030, 20480)]
 
 
