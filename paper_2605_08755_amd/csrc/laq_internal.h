@@ -148,6 +148,23 @@ hipError_t launch_linear_stream(const StreamPlan& p, const uint16_t* x, const ui
                                 const uint16_t* scales, const uint8_t* zeros, uint16_t* y, float* part, int M,
                                 int64_t N, int G, hipStream_t stream, const LaunchEvents& ev);
 
+// Kernel of a matrix-core linear, a pure function of the shape and of whether
+// there is a workspace for the split-K sums.
+enum class MfmaRoute : int {
+  Stream,        // linear_stream.hip, outputs
+  Share,         // three tiles per block share the quads' slabs, one wave per (tile, quad)
+  QuadWave,      // one tile per block, one wave per quad
+  QuadWaveRegs,  // the same in 64 registers
+  QuadWaveCodes, // the same, codes through LDS
+  Walk4,         // four tiles per block walking K
+  Walk8,         // eight
+  SplitStream,   // K ranges in linear_stream.hip, reduction
+  Split,         // K ranges of at most five quads in blocks of four tiles, reduction
+  OneTileCodes,  // one tile per block, waves splitting its quads, codes through LDS
+  TwoTiles,      // two tiles per block, waves splitting the quads
+};
+MfmaRoute mfma_route(int bits, int M, int64_t N, int64_t K, bool workspace);
+
 // calls[i].{x, qw, scales, zeros, y, N, G} filled in by the caller; count in 1..kMaxGroup.
 template <int BITS>
 hipError_t launch_linear_group(LinearCall* calls, int count, int M, hipStream_t stream, const LaunchEvents& ev);

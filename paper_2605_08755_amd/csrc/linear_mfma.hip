@@ -978,28 +978,119 @@ SplitPlan mfma_split_plan(int M, int64_t N, int G) {
   return p;
 }
 
+namespace {
+
 // Where keeping the activations in registers over many tiles (linear_stream.hip)
-// is the faster way: enough (tile, quad) units that a block walks several
-// tiles, more of them for fewer activation rows, whose slabs cost the
-// tile-by-tile kernels less.  Measured on MI355X, tile by tile -> stream, W3:
-// M = 16: 8192 x 4096 (4096 units) 9.4 -> 6.4 us, 5120 x 8192 (5120) 13.9 -> 11.5,
-// 10240 x 5120 (6400) 15.5 -> 11.0, 51200 x 5120 39.1 -> 28.2, but 2560 x 6144
-// (1920) 6.4 -> 7.0; M = 8: 5120 x 8192 11.1 -> 9.9, 10240 x 5120 10.8 -> 9.8, but
-// 8192 x 4096 6.9 -> 7.5, 19456 x 2560 (6080) 9.3 -> 10.1; M = 4: 24576 x 4096
-// (12288) 13.9 -> 11.8, 51200 x 5120 34.5 -> 26.4, 5120 x 8192 10.4 -> 8.9 (rows past
-// the one-wave-per-quad kernel's ten quads), but 30000 x 3200 (13125) 14.4 -> 14.9,
-// 10240 x 5120 9.8 -> 9.6, 8192 x 4096 6.1 -> 6.8.
-bool stream_pays(int M, int64_t tiles, int nq) {
+// is the faster way: from a count of (tile, quad) units on, with which a block
+// walks several tiles.  The lines lie where the two ways cross, measured on
+// MI355X as the ratio of the streaming kernel's time to the tile by tile
+// kernels' over 4000 to 40000 units:
+//  - M > 8 (slabs of 16 rows cost the others most): 0.7 - 0.9 from 4096 units
+//    (8192 x 4096 W3 9.4 -> 6.8 us); five quads 0.93 from 8200 (1.08 at 6145),
+//    in W4 with a partial last quad 1.04 until 16384, 1.00 at 25000.
+//  - 4 < M <= 8: rows of whole cache lines (G % 8 == 0, which the loads of a
+//    pair of quads share) 0.91 - 1.03 at 6144, 0.8 - 0.9 at 12288 (24576 x 4096 W3
+//    17.4 -> 13.4 us).  Others: W3 1.0 - 1.2 at 6144 - 10240, five and six quads
+//    0.9 - 0.97 at 12288, seven and more 0.95 - 0.99 at 16384, nine (nine waves a
+//    block, three on one SIMD) 1.03 there, 0.93 at 24576; W4 0.9 - 1.0 at 10240,
+//    five quads 0.86 - 1.00 at 16384.
+//  - M <= 4: whole lines 0.8 - 1.0 at 12288; others W3 0.92 - 1.05 at 16384, below 1
+//    at 24576, nine quads 1.00 at 40000; W4 0.77 - 1.04 at 16384.
+//  - More than ten quads (no one-wave-per-quad kernel there): 0.8 - 1.0 from 4096
+//    units, once there are more tiles than compute units (256 tiles of 16 quads
+//    1.04 - 1.16, 257 0.83 - 0.92).
+//  - 1024 tiles are one round of the four-tiles-per-block kernel on 256 compute
+//    units, which only few shapes beat: W3 up to eleven quads and at 13 1.04 - 1.2
+//    (eight quads 0.96), W4 at M > 8 with nine and eleven quads 1.06 - 1.10.
+bool stream_pays(int bits, int M, int64_t tiles, int nq, int G) {
   const int64_t units = tiles * nq;
   if (nq < 5) return false;
-  if (nq > kQuadWaveMax) return units >= 4096;
-  if (M > 8) return units >= (nq > 5 ? 4096 : 8192);
-  if (M > 4) return units >= 6144;
-  return units >= (nq >= 8 ? 12288 : 16384);
+  if (tiles == kMfmaShareMinTiles && (bits == 3 ? nq < 12 || nq == 13 : M > 8 && (nq == 9 || nq == 11))) return false;
+  if (nq > kQuadWaveMax) return units >= 4096 && tiles > 256;
+  if (M > 8) return units >= (nq > 5 ? 4096 : bits == 4 && G % 4 ? 24576 : 8192);
+  const bool whole = G % 8 == 0;
+  if (M > 4) {
+    if (whole) return units >= (nq == 8 ? 6656 : 6144);
+    if (bits == 3) return units >= (nq <= 6 ? 12288 : nq == 9 ? 20480 : 16384);
+    return units >= (nq == 5 ? 16384 : 10240);
+  }
+  if (whole) return units >= (nq >= 8 ? 12288 : 16384);
+  return units >= (bits == 4 ? 16384 : nq == 9 ? 40960 : 20480);
 }
 
 constexpr int64_t kStreamSplitMinUnits = 2048;
 constexpr int kStreamSplitMaxRanges = 16;  // at least 16 blocks per range
+
+// K ranges of up to 16 quads in the streaming kernel, given enough units
+// (fewer ranges than linear_mfma_split_kernel's, so they fit the same
+// workspace).  Measured on MI355X, both kernels of the split, W3: 5120 x 25600 at
+// M = 3 / 8 / 16 27.1 / 28.1 / 29.9 -> 20.3 / 23.0 / 21.4 us, 1024 x 25600 (3200 units) at
+// M = 4 11.1 -> 8.8.  W3 at M > 8 has 1.02 - 1.06 of the other kernel's time at 2048
+// units and up to 1.10 where a few tiles more than a range has blocks make a
+// second round (70 of 64: 1.10, 100 of 85: 1.03).
+int stream_split_ranges(int bits, int M, int64_t tiles, int nq) {
+  const int ranges = (nq + 15) / 16;
+  const int64_t units = tiles * nq;
+  if (units < kStreamSplitMinUnits || ranges > kStreamSplitMaxRanges) return 0;
+  const int64_t blocks = 256 / ranges;
+  if (bits == 3 && M > 8 && (units < 3072 || (tiles > blocks && 3 * tiles < 4 * blocks))) return 0;
+  return ranges;
+}
+
+// Activation rows staged by the one-wave-per-quad kernels.
+int slab_rows(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
+
+}  // namespace
+
+MfmaRoute mfma_route(int bits, int M, int64_t N, int64_t K, bool workspace) {
+  const int G = (int)(K / 128);
+  const int nq = (G + 3) / 4;
+  const int64_t tiles = (N + 15) / 16;
+  constexpr size_t kLds = (size_t)kBlockLdsU4 * 16;
+  if (stream_pays(bits, M, tiles, nq, G) && stream_plan(bits, M, N, G, 1).W > 0) return MfmaRoute::Stream;
+  // Many tiles, rows of at most five quads, M > 4 (W4: M > 8; at M <= 8 the
+  // one-tile blocks below are faster for W4).
+  if (tiles >= kMfmaShareMinTiles && nq <= 5 && M > (bits == 4 ? 8 : 4)) return MfmaRoute::Share;
+  // Rows of at most kQuadWaveMax quads whose activation slabs fit in LDS
+  // (measured on MI355X against the kernels below: faster for every Qwen3-4B
+  // projection from M = 3 that the sharing kernel above does not take).
+  const size_t lds = (size_t)nq * slab_rows(M) * 1024;
+  if (nq <= kQuadWaveMax && lds <= kLds && (tiles < kMfmaShareMinTiles || M <= 8)) {
+    // More waves than stay resident at 5 per SIMD (the up-front fragments'
+    // register count): the 64-register form, 8 per SIMD (measured on MI355X:
+    // Qwen3-4B gate|up at M = 4, 1216 tiles x 5 waves, 10.8 -> 8.6 us; the smaller
+    // projections are 1-2 % faster with the fragments up front).
+    if (tiles * nq > (int64_t)kQuadWaveResident) return MfmaRoute::QuadWaveRegs;
+    // Codes through LDS while the blocks that then fit on the compute units
+    // still hold every tile at once; in W3 from eight quads (fewer: 536 x 768 at
+    // M = 9 2.91 -> 2.98 us, 1.00 - 1.02 of the register form up to seven quads).
+    const size_t lds_codes = lds + (size_t)nq * unit_bytes(bits);
+    return (bits == 4 || nq >= 8) && tiles <= 256 * (int64_t)(kLds / lds_codes) ? MfmaRoute::QuadWaveCodes
+                                                                                 : MfmaRoute::QuadWave;
+  }
+  // Many tiles, longer rows: blocks of four or eight tiles walking K share
+  // each activation slab through LDS.
+  if (tiles >= kMfmaShareMinTiles) return tiles >= 3072 ? MfmaRoute::Walk8 : MfmaRoute::Walk4;
+  // Fewer tiles, long rows, a workspace: K ranges, whose partial sums a second
+  // kernel adds in order.
+  const SplitPlan sp = mfma_split_plan(M, N, G);
+  if (sp.S > 1 && workspace) {
+    const int ranges = stream_split_ranges(bits, M, tiles, nq);
+    const StreamPlan st = ranges ? stream_plan(bits, M, N, G, ranges) : StreamPlan{};
+    return st.W > 0 && st.ranges <= sp.S ? MfmaRoute::SplitStream : MfmaRoute::Split;
+  }
+  // Codes through LDS, one tile per block, while the blocks that fit on the
+  // compute units hold every tile at once (measured on MI355X, M = 4 / 16:
+  // 4096 x 16384 18.4 / 23.6 -> 10.2 / 13.9 us, against two tiles per block on half
+  // the compute units; 1024 x 8192 5.8 / 7.6 -> 5.0 / 6.0; 2560 x 9728 7.2 / 9.6 ->
+  // 7.1 / 9.0).
+  const size_t lds_codes = (size_t)mfma_codes_waves(bits, M, nq) * (M * 1024 + unit_bytes(bits));
+  if (tiles <= 256 * (int64_t)(kLds / lds_codes)) return MfmaRoute::OneTileCodes;
+  // More than 256 tiles, rows of more than kQuadWaveMax quads: two tiles per
+  // block share each activation fragment.  (At most M tiles per wave: a wave's
+  // partials of two tiles, 2 KiB, reuse its M KiB slab.)
+  return MfmaRoute::TwoTiles;
+}
 
 template <int BITS>
 hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const uint16_t* scales,
@@ -1009,139 +1100,106 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
   const int G = (int)(K / 128);
   const int nq = (G + 3) / 4;
   const int64_t tiles = (N + 15) / 16;
-  if (stream_pays(M, tiles, nq))
-    if (const StreamPlan st = stream_plan(BITS, M, N, G, 1); st.W > 0)
-      return launch_linear_stream<BITS>(st, x, qweight, scales, zeros, y, nullptr, M, N, G, stream, ev);
-  // Many tiles, rows of at most five quads, M > 4 (W4: M > 8; at M <= 8 the
-  // one-tile blocks below are faster for W4): three tiles per block share
-  // the quads' slabs, one wave per (tile, quad).
-  if (tiles >= kMfmaShareMinTiles && nq <= 5 && M > (BITS == 4 ? 8 : 4)) {
-    constexpr int TPB = 3;
-    const int nblocks = (int)((tiles + TPB - 1) / TPB);
-    const dim3 grid(xcd_grid(nblocks)), blk(64 * TPB * nq);
-    if (M > 8)
-      launch(linear_mfma_quad_share_kernel<BITS, 16, TPB>, grid, blk, (uint32_t)nq * 16 * 1024, stream, ev, x,
-             qweight, scales, zeros, y, M, (int)N, G, nblocks);
-    else
-      launch(linear_mfma_quad_share_kernel<BITS, 8, TPB>, grid, blk, (uint32_t)nq * 8 * 1024, stream, ev, x,
-             qweight, scales, zeros, y, M, (int)N, G, nblocks);
-    return hipGetLastError();
-  }
-  // Rows of at most kQuadWaveMax quads whose activation slabs fit in LDS: one
-  // tile per block, one wave per quad (measured on MI355X against the kernels
-  // below: faster for every Qwen3-4B projection from M = 3 that the sharing
-  // kernel above does not take).
-  {
-    const int MT = M <= 4 ? 4 : M <= 8 ? 8 : 16;
-    const size_t lds = (size_t)nq * MT * 1024;
-    if (nq <= kQuadWaveMax && lds <= (size_t)kBlockLdsU4 * 16 && (tiles < kMfmaShareMinTiles || M <= 8)) {
-      const int nblocks = (int)tiles;
-      const dim3 grid(xcd_grid(nblocks)), blk(64 * nq);
-      // More waves than stay resident at 5 per SIMD (the up-front fragments'
-      // register count): the 64-register form, 8 per SIMD (measured on
-      // MI355X: Qwen3-4B gate|up at M = 4, 1216 tiles x 5 waves, 10.8 -> 8.6 us;
-      // the smaller projections are 1-2 % faster with the fragments up front).
-      const bool lowreg = tiles * nq > (int64_t)kQuadWaveResident;
-      // Codes through LDS while the blocks that then fit on the compute units
-      // still hold every tile at once.
-      const size_t lds_codes = lds + (size_t)nq * unit_bytes(BITS);
-      const bool codes_lds = !lowreg && tiles <= 256 * (int64_t)((size_t)kBlockLdsU4 * 16 / lds_codes);
-#define LAQ_QW_K(MTV, LRV, CLV, LDSV)                                                                             \
-  launch(linear_mfma_quad_wave_kernel<BITS, MTV, LRV, CLV>, grid, blk, (uint32_t)(LDSV), stream, ev, x, qweight, \
-         scales, zeros, y, M, (int)N, G, nblocks)
-#define LAQ_QW(MTV)                                            \
-  do {                                                         \
-    if (lowreg) LAQ_QW_K(MTV, true, false, lds);               \
-    else if (codes_lds) LAQ_QW_K(MTV, false, true, lds_codes); \
-    else LAQ_QW_K(MTV, false, false, lds);                     \
-  } while (0)
-      if (MT == 4) LAQ_QW(4);
-      else if (MT == 8) LAQ_QW(8);
-      else LAQ_QW(16);
-#undef LAQ_QW
-#undef LAQ_QW_K
-      return hipGetLastError();
-    }
-  }
-  // Many tiles, longer rows: blocks of four or eight tiles walking K share
-  // each activation slab through LDS.
-  if (tiles >= kMfmaShareMinTiles) {
-    const int tb = tiles >= 3072 ? 8 : 4;
-    const int nblocks = (int)((tiles + tb - 1) / tb);
-    if (tb == 8)
-      launch(linear_mfma_tiles_kernel<BITS, 8>, dim3(xcd_grid(nblocks)), dim3(512), kSlabLdsBytes, stream, ev, x,
-             qweight, scales, zeros, y, M, (int)N, G, nblocks);
-    else
-      launch(linear_mfma_tiles_kernel<BITS, 4>, dim3(xcd_grid(nblocks)), dim3(256), kSlabLdsBytes, stream, ev, x,
-             qweight, scales, zeros, y, M, (int)N, G, nblocks);
-    return hipGetLastError();
-  }
-  // Fewer tiles, long rows, a workspace: split K over blocks of four tiles
-  // that request their whole K range at once; a second kernel adds the
-  // ranges' partial sums in order.
   const SplitPlan sp = mfma_split_plan(M, N, G);
-  if (sp.S > 1 && workspace && workspace_bytes >= split_workspace_bytes(sp, M, N)) {
-    const int64_t MN = (int64_t)M * N;
-    const dim3 rgrid((unsigned)((MN + 1023) / 1024));
-    LaunchEvents e1, e2;  // the measurement hook spans both kernels
-    e1.start = ev.start;
-    e2.stop = ev.stop;
-    // Enough (tile, quad) units: ranges of up to 16 quads in the streaming
-    // kernel (fewer ranges than below, so they fit the same workspace).
-    // Measured on MI355X, both kernels of the split: 5120 x 25600 at M = 3 / 8 / 16
-    // 27.1 / 28.3 / 29.9 -> 18.7 / 21.4 / 19.8 us, 8192 x 20480 at M = 8 34.0 ->
-    // 26.2, 1024 x 25600 (3200 units) at M = 4 11.2 -> 8.9.
-    const int ranges = (nq + 15) / 16;
-    const StreamPlan st = tiles * nq >= kStreamSplitMinUnits && ranges <= kStreamSplitMaxRanges
-                              ? stream_plan(BITS, M, N, G, ranges)
-                              : StreamPlan{};
-    if (st.W > 0 && st.ranges <= sp.S) {
-      const hipError_t e =
-          launch_linear_stream<BITS>(st, x, qweight, scales, zeros, nullptr, workspace, M, N, G, stream, e1);
-      if (e != hipSuccess) return e;
-      launch(splitk_reduce_kernel, rgrid, dim3(256), 0, stream, e2, (const float*)workspace, y, st.ranges, MN);
-      return hipGetLastError();
+  const MfmaRoute route =
+      mfma_route(BITS, M, N, K, workspace && workspace_bytes >= split_workspace_bytes(sp, M, N));
+  const int MT = slab_rows(M);
+  const size_t quad_lds = (size_t)nq * MT * 1024;
+  const size_t quad_codes_lds = quad_lds + (size_t)nq * unit_bytes(BITS);
+#define LAQ_QW(MTV, LRV, CLV, LDSV)                                                                             \
+  launch(linear_mfma_quad_wave_kernel<BITS, MTV, LRV, CLV>, dim3(xcd_grid(tiles)), dim3(64 * nq), (uint32_t)(LDSV), \
+         stream, ev, x, qweight, scales, zeros, y, M, (int)N, G, (int)tiles)
+  switch (route) {
+    case MfmaRoute::Stream:
+      return launch_linear_stream<BITS>(stream_plan(BITS, M, N, G, 1), x, qweight, scales, zeros, y, nullptr, M, N, G,
+                                        stream, ev);
+    case MfmaRoute::Share: {
+      constexpr int TPB = 3;
+      const int nblocks = (int)((tiles + TPB - 1) / TPB);
+      const dim3 grid(xcd_grid(nblocks)), blk(64 * TPB * nq);
+      if (M > 8)
+        launch(linear_mfma_quad_share_kernel<BITS, 16, TPB>, grid, blk, (uint32_t)quad_lds, stream, ev, x, qweight,
+               scales, zeros, y, M, (int)N, G, nblocks);
+      else
+        launch(linear_mfma_quad_share_kernel<BITS, 8, TPB>, grid, blk, (uint32_t)quad_lds, stream, ev, x, qweight,
+               scales, zeros, y, M, (int)N, G, nblocks);
+      break;
     }
-    const int nblocks = sp.tile_blocks * sp.S;
-    const dim3 grid(xcd_grid(nblocks)), blk(64 * kFullTiles);
-    const uint32_t lds = (uint32_t)sp.qs * kSlabBytes;
-    switch (sp.qs) {
-      case 1: launch(linear_mfma_split_kernel<BITS, 1>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
-      case 2: launch(linear_mfma_split_kernel<BITS, 2>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
-      case 3: launch(linear_mfma_split_kernel<BITS, 3>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
-      case 4: launch(linear_mfma_split_kernel<BITS, 4>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
-      default: launch(linear_mfma_split_kernel<BITS, 5>, grid, blk, lds, stream, e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace); break;
+    case MfmaRoute::QuadWave:
+      if (MT == 4) LAQ_QW(4, false, false, quad_lds);
+      else if (MT == 8) LAQ_QW(8, false, false, quad_lds);
+      else LAQ_QW(16, false, false, quad_lds);
+      break;
+    case MfmaRoute::QuadWaveRegs:
+      if (MT == 4) LAQ_QW(4, true, false, quad_lds);
+      else if (MT == 8) LAQ_QW(8, true, false, quad_lds);
+      else LAQ_QW(16, true, false, quad_lds);
+      break;
+    case MfmaRoute::QuadWaveCodes:
+      if (MT == 4) LAQ_QW(4, false, true, quad_codes_lds);
+      else if (MT == 8) LAQ_QW(8, false, true, quad_codes_lds);
+      else LAQ_QW(16, false, true, quad_codes_lds);
+      break;
+    case MfmaRoute::Walk4:
+    case MfmaRoute::Walk8: {
+      const int tb = route == MfmaRoute::Walk8 ? 8 : 4;
+      const int nblocks = (int)((tiles + tb - 1) / tb);
+      if (tb == 8)
+        launch(linear_mfma_tiles_kernel<BITS, 8>, dim3(xcd_grid(nblocks)), dim3(512), kSlabLdsBytes, stream, ev, x,
+               qweight, scales, zeros, y, M, (int)N, G, nblocks);
+      else
+        launch(linear_mfma_tiles_kernel<BITS, 4>, dim3(xcd_grid(nblocks)), dim3(256), kSlabLdsBytes, stream, ev, x,
+               qweight, scales, zeros, y, M, (int)N, G, nblocks);
+      break;
     }
-    launch(splitk_reduce_kernel, rgrid, dim3(256), 0, stream, e2, (const float*)workspace, y, sp.S, MN);
-    return hipGetLastError();
+    case MfmaRoute::SplitStream:
+    case MfmaRoute::Split: {
+      const int64_t MN = (int64_t)M * N;
+      LaunchEvents e1, e2;  // the measurement hook spans both kernels
+      e1.start = ev.start;
+      e2.stop = ev.stop;
+      int S = sp.S;
+      if (route == MfmaRoute::SplitStream) {
+        const StreamPlan st = stream_plan(BITS, M, N, G, stream_split_ranges(BITS, M, tiles, nq));
+        const hipError_t e =
+            launch_linear_stream<BITS>(st, x, qweight, scales, zeros, nullptr, workspace, M, N, G, stream, e1);
+        if (e != hipSuccess) return e;
+        S = st.ranges;
+      } else {
+        // Blocks of four tiles that request their whole K range at once.
+        const int nblocks = sp.tile_blocks * sp.S;
+#define LAQ_SPLIT(NQV)                                                                                               \
+  launch(linear_mfma_split_kernel<BITS, NQV>, dim3(xcd_grid(nblocks)), dim3(64 * kFullTiles), NQV * kSlabBytes, stream, \
+         e1, x, qweight, scales, zeros, M, (int)N, G, sp.tile_blocks, nblocks, workspace)
+        switch (sp.qs) {
+          case 1: LAQ_SPLIT(1); break;
+          case 2: LAQ_SPLIT(2); break;
+          case 3: LAQ_SPLIT(3); break;
+          case 4: LAQ_SPLIT(4); break;
+          default: LAQ_SPLIT(5); break;
+        }
+#undef LAQ_SPLIT
+      }
+      launch(splitk_reduce_kernel, dim3((unsigned)((MN + 1023) / 1024)), dim3(256), 0, stream, e2,
+             (const float*)workspace, y, S, MN);
+      break;
+    }
+    case MfmaRoute::OneTileCodes: {
+      const int W = mfma_codes_waves(BITS, M, nq);
+      launch(linear_mfma_kernel<BITS, 1, true>, dim3(xcd_grid(tiles)), dim3(64 * W),
+             (uint32_t)(W * (M * 1024 + unit_bytes(BITS))), stream, ev, x, qweight, scales, zeros, y, M, (int)N, G,
+             (int)tiles);
+      break;
+    }
+    case MfmaRoute::TwoTiles: {
+      const int W = mfma_block_waves(M, nq);
+      const int nblocks = (int)((tiles + 1) / 2);
+      launch(linear_mfma_kernel<BITS, 2, false>, dim3(xcd_grid(nblocks)), dim3(64 * W),
+             (uint32_t)W * M * kSlabRowU4 * 16, stream, ev, x, qweight, scales, zeros, y, M, (int)N, G, nblocks);
+      break;
+    }
   }
-  // Codes through LDS, one tile per block, while the blocks that fit on the
-  // compute units hold every tile at once (measured on MI355X, M = 4 / 16:
-  // 4096 x 16384 18.4 / 23.6 -> 10.2 / 13.9 us, against two tiles per block on half
-  // the compute units; 1024 x 8192 5.8 / 7.6 -> 5.0 / 6.0; 2560 x 9728 7.2 / 9.6 ->
-  // 7.1 / 9.0).
-  const int Wc = mfma_codes_waves(BITS, M, nq);
-  const size_t lds_codes = (size_t)Wc * (M * 1024 + unit_bytes(BITS));
-  if (tiles <= 256 * (int64_t)((size_t)kBlockLdsU4 * 16 / lds_codes)) {
-    launch(linear_mfma_kernel<BITS, 1, true>, dim3(xcd_grid(tiles)), dim3(64 * Wc), (uint32_t)lds_codes, stream, ev, x,
-           qweight, scales, zeros, y, M, (int)N, G, (int)tiles);
-    return hipGetLastError();
-  }
-  // Two tiles per block share each activation fragment when rows are long
-  // (the fragments then outweigh the weights) and there are enough tiles to
-  // keep a block on every compute unit (measured on MI355X).  (At most M
-  // tiles per wave: a wave's TW KiB of partials reuse its M KiB slab.)
-  const int TW = min(M, (tiles >= 256 && G >= 32) ? 2 : 1);
-  const int W = mfma_block_waves(M, nq);
-  const int nblocks = (int)((tiles + TW - 1) / TW);
-  const unsigned blocks = xcd_grid(nblocks);
-  const uint32_t lds = (uint32_t)W * M * kSlabRowU4 * 16;
-  if (TW == 2)
-    launch(linear_mfma_kernel<BITS, 2, false>, dim3(blocks), dim3(64 * W), lds, stream, ev, x, qweight, scales, zeros, y, M,
-           (int)N, G, nblocks);
-  else
-    launch(linear_mfma_kernel<BITS, 1, false>, dim3(blocks), dim3(64 * W), lds, stream, ev, x, qweight, scales, zeros, y,
-           M, (int)N, G, nblocks);
+#undef LAQ_QW
   return hipGetLastError();
 }
 
