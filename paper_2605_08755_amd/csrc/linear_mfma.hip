@@ -25,6 +25,8 @@
 // quad at a time, two quads ahead (many tiles, longer rows).  Calls with many
 // (tile, quad) units go to linear_stream.hip instead.  Every reduction order
 // is fixed, so results are deterministic.
+#include <algorithm>
+
 #include "mfma_util.h"
 
 namespace laq {
@@ -637,8 +639,11 @@ __global__ __launch_bounds__(1024 / TW) void linear_mfma_kernel(
 
 // Several independent calls in one launch (one 16-row tile per block); the
 // call of block b is picked with constant indices, as in the flat kernel.
+// (The register bound: one of the two bit widths otherwise takes 81, five waves
+// per SIMD instead of six; 2 x 19200 x 4096 W3 at M = 5 25.8 -> 23.0 us.)
+constexpr int kGroupWavesPerSimd = 6;
 template <int BITS>
-__global__ __launch_bounds__(1024) void linear_mfma_group_kernel(const LinearGroup grp, int M) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kGroupWavesPerSimd))) void linear_mfma_group_kernel(const LinearGroup grp, int M) {
   const int b = xcd_block(grp.blocks);
   if (b >= grp.blocks) return;  // idle slot of the XCD-rounded grid
   LinearCall c = grp.call[0];
@@ -1203,6 +1208,36 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
   return hipGetLastError();
 }
 
+// Blocks of W waves that stay resident on a compute unit: by LDS (allocated in
+// pieces of 1280 bytes) and by registers, where a SIMD holds `waves`; four or
+// more waves of a block go to the SIMDs in turn from the first.
+static int resident_blocks(size_t lds, int W, int waves) {
+  const int by_lds = (int)((size_t)kBlockLdsU4 * 16 / ((lds + 1279) / 1280 * 1280));
+  return std::min(by_lds, W < 4 ? waves * (4 / W) : waves / ((W + 3) / 4));
+}
+
+// Whether a group (`tiles` tiles in all, nq quads in its longest row) takes the
+// one-wave-per-quad kernel, and in which form: 0 the up-front one, 1 the one in
+// 64 registers, where the tiles are too many to be resident at once in the
+// first; -1: the kernel whose waves walk several quads.  One wave per quad loads
+// everything at once, so it is ahead while every tile is resident at once, or
+// as many blocks as of the other kernel, whose slabs have M rows instead of 4, 8
+// or 16.  Measured on MI355X, walking -> one wave per quad: W3 M = 16 2 x 9728 x
+// 2560 15.3 -> 13.3 us, M = 4 2 x 9728 x 3072 13.8 -> 10.2; but M = 9 2 x 9728 x 4096
+// (one block resident instead of two) 16.7 -> 22.7, 2 x 9728 x 1024 (four, seven)
+// 6.2 -> 7.4, 4096 + 1024 rows x 3072 (one, two) 6.6 -> 7.9; W4 M = 5 2 x 9728 x 4096
+// (two, three) 14.7 -> 16.4.  Over 2000 groups of 1 to 19 quads the choice took
+// at most 1.08 of the better one's time, 0.95 of the walking one's on average.
+int mfma_group_quad_wave(int M, int64_t tiles, int nq) {
+  const size_t lds = (size_t)nq * slab_rows(M) * 1024;
+  if (nq > kQuadWaveMax || lds > (size_t)kBlockLdsU4 * 16) return -1;
+  const int regs64 = tiles > 256 * (int64_t)resident_blocks(lds, nq, 5);
+  const int quad = resident_blocks(lds, nq, regs64 ? 8 : 5);
+  const int W = mfma_block_waves(M, nq);
+  const int walk = resident_blocks((size_t)W * M * 1024, W, kGroupWavesPerSimd);
+  return tiles <= 256 * (int64_t)quad || quad >= walk ? regs64 : -1;
+}
+
 template <int BITS>
 hipError_t launch_linear_mfma_group(LinearCall* calls, int count, int M, hipStream_t stream,
                                     const LaunchEvents& ev) {
@@ -1219,15 +1254,12 @@ hipError_t launch_linear_mfma_group(LinearCall* calls, int count, int M, hipStre
   }
   grp.count = count;
   grp.blocks = (int)blocks;
-  // Rows of at most kQuadWaveMax quads: one wave per quad, as for one call.
-  // (Measured on MI355X, W4 at M = 4: gate and up 2 x 9728 x 2560 11.9 us on the
-  // VALU kernel, q, k, v 7.2 us.)
-  const int MT = M <= 4 ? 4 : M <= 8 ? 8 : 16;
-  const size_t lds = (size_t)nq_max * MT * 1024;
-  if (nq_max <= kQuadWaveMax && lds <= (size_t)kBlockLdsU4 * 16) {
+  if (const int regs64 = mfma_group_quad_wave(M, blocks, nq_max); regs64 >= 0) {
+    const int MT = slab_rows(M);
+    const size_t lds = (size_t)nq_max * MT * 1024;
     grp.waves = nq_max;
     const dim3 grid(xcd_grid(blocks)), blk(64 * nq_max);
-    const bool lowreg = blocks * nq_max > (int64_t)kQuadWaveResident;
+    const bool lowreg = regs64;
 #define LAQ_QWG(MTV)                                                                                                  \
   do {                                                                                                                \
     if (lowreg) launch(linear_mfma_quad_wave_group_kernel<BITS, MTV, true>, grid, blk, (uint32_t)lds, stream, ev, grp, M); \

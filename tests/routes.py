@@ -37,3 +37,10 @@ def stream_plan(bits, M, N, G, ranges):
 def split_plan(M, N, G):
     i = ctypes.c_int
     return _bind("_ZN3laq15mfma_split_planEili", SplitPlan, i, ctypes.c_int64, i)(M, N, G)
+
+
+def group_quad_wave(M, tiles, nq):
+    """Form of the one-wave-per-quad kernel that a group takes (0 up-front, 1 in
+    64 registers), or -1: the kernel whose waves walk several quads."""
+    i = ctypes.c_int
+    return _bind("_ZN3laq20mfma_group_quad_waveEili", i, i, ctypes.c_int64, i)(M, tiles, nq)

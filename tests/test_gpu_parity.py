@@ -16,6 +16,7 @@ import torch
 import oracle
 from oracle.compare import linear_check
 from paper_2605_08755_amd import inputs, laq
+from routes import group_quad_wave
 
 pytestmark = pytest.mark.gpu
 
@@ -711,8 +712,8 @@ def _group_case(bits, specs, M, cfg):
 def test_group_qkv(bits, M):
     """q, k, v of a Qwen3-4B layer (same activations) as one launch.  Up to
     M = 2 the grouped and the single calls run the same VALU kernel body and
-    agree bit for bit; at M = 3 and 4 the group stays on the VALU kernel
-    (its rows are short) while a single call takes the matrix cores."""
+    agree bit for bit; from M = 3 both take the matrix cores, one wave per
+    quad."""
     say("group qkv", bits, M)
     ys, singles, refs = _group_case(bits, [(4096, 2560, 0), (1024, 2560, 0), (1024, 2560, 0)], M, cfg=40)
     for y, y1, ref in zip(ys, singles, refs):
@@ -736,6 +737,46 @@ def test_group_mixed(bits, M):
         assert r["ok"], r
         if M <= 2:
             assert np.array_equal(y.view(np.uint16), y1.view(np.uint16))
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("M", [3, 4, 8, 9, 16])
+def test_group_row_lengths(bits, M):
+    """Rows of 1, 2, 5 and 10 quads in one launch of the one-wave-per-quad
+    kernel (waves past a shorter row's quads only join the barrier), ragged N,
+    partial last quads, separate activations."""
+    say("group row lengths", bits, M)
+    specs = [(300, 4992, 0), (17, 128, 1), (257, 640, 2), (1, 2560, 3), (130, 2176, 4)]
+    assert group_quad_wave(M, sum(-(-N // 16) for N, _, _ in specs), 10) == 0
+    ys, _, refs = _group_case(bits, specs, M, cfg=43)
+    for y, ref in zip(ys, refs):
+        r = linear_check(y, ref)
+        assert r["ok"], r
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("M,form", [(3, 1), (8, 1), (9, -1), (16, 1)])
+def test_group_many_tiles(bits, M, form):
+    """More tiles than are resident in the up-front form: the 64-register form,
+    or at M = 9 the kernel whose waves walk several quads; one call with shorter
+    rows and a ragged last tile.  Repeated weight rows give the same bits,
+    repeated calls too, and nothing is written past the outputs."""
+    say("group many tiles", bits, M)
+    shapes = [(9728, 2560), (9731, 640), (9728, 2560)]
+    assert group_quad_wave(M, sum(-(-N // 16) for N, _ in shapes), 5) == form
+    cases = [_repeated_rows(bits, N, K) for N, K in shapes]
+    xs = [inputs.activations(M, K, cfg=44, layer=i) for i, (_, K) in enumerate(shapes)]
+    calls = [(to_dev(x), *c[4]) for x, c in zip(xs, cases)]
+    bufs = [torch.full((M * N + 64,), 3.0, dtype=torch.float16, device=DEV) for N, _ in shapes]
+    ys = laq.linear_group(calls, bits, outs=[b[:M * N].view(M, N) for b, (N, _) in zip(bufs, shapes)])
+    again = laq.linear_group(calls, bits)
+    torch.cuda.synchronize()
+    for x, (codes, s, z, rows, _), y, y2, buf in zip(xs, cases, ys, again, bufs):
+        assert torch.equal(y, y2) and torch.all(buf[y.numel():] == 3.0)
+        y = y.cpu().numpy()
+        assert np.array_equal(y, y[:, rows])
+        r = linear_check(y[:, :len(codes)], oracle.linear(x, codes, s, z))
+        assert r["ok"], r
 
 
 @pytest.mark.parametrize("bits", [3, 4])

@@ -4,7 +4,7 @@ import random
 
 import pytest
 
-from routes import route, split_plan, stream_plan
+from routes import group_quad_wave, route, split_plan, stream_plan
 
 LDS = 160 * 1024
 
@@ -103,3 +103,17 @@ LINES = [
 @pytest.mark.parametrize("shape,kernel", LINES)
 def test_measured_lines(shape, kernel):
     assert route(*shape) == kernel
+
+
+# (M, tiles, quads of the longest row) -> form, on both sides of the lines.
+GROUP_LINES = [
+    ((4, 384, 5), 0), ((4, 1216, 5), 1), ((16, 1216, 5), 1), ((9, 1216, 5), -1), ((9, 512, 5), 0), ((9, 1216, 8), -1),
+    ((9, 256, 8), 0), ((16, 1216, 8), 1), ((9, 320, 6), -1), ((14, 320, 6), 1), ((9, 1216, 2), -1), ((16, 1216, 2), 1),
+    ((5, 1216, 8), -1), ((8, 1216, 8), 1), ((4, 256, 10), 0), ((4, 320, 10), 1), ((4, 3200, 10), -1), ((4, 4, 11), -1),
+    ((9, 2400, 1), -1), ((16, 2400, 1), 1),
+]
+
+
+@pytest.mark.parametrize("shape,form", GROUP_LINES)
+def test_group_lines(shape, form):
+    assert group_quad_wave(*shape) == form
