@@ -475,9 +475,14 @@ __global__ __launch_bounds__(64 * R) void attn_qkv_partial_kernel(
 //    one column n) lets values come straight into registers: lane (n, j) loads
 //    dimensions 8n .. 8n+7 of one row, four whole rows per instruction, and
 //    element e is the operand of the columns {8n + e}.
-// The next step's loads are in flight while a step is computed.  The token at
-// pos is not read back from the cache: wave 0 of the last chunk starts from it
-// (maximum its score, denominator 1, value sums its value row).
+// The next step's loads are in flight while a step is computed: the waits count
+// instructions, so a step is compiled once with and once without later loads.
+// (Measured on MI355X against one form for both, which waited for all loads before
+// the value sums of every other step: 64:8 at 12288 21.4 -> 19.9 us, 32:8 at 32767
+// 33.5 -> 32.5, 8:1 at 16000 12.6 -> 12.1; with an odd count of steps per wave 32:8
+// at 24000 26.7 -> 27.4, 4:4 at 40000 24.0 -> 24.6.)
+// The token at pos is not read back from the cache: wave 0 of the last chunk
+// starts from it (maximum its score, denominator 1, value sums its value row).
 constexpr int kFlashWaves = 8;
 constexpr int kFlashStep = 32;                           // positions per wave and step
 constexpr int kFlashRow = (kFlashStep + 4) * 4;          // bytes of a row of probabilities (4 words of padding)
@@ -548,6 +553,7 @@ __device__ __forceinline__ void flash_block(
       __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void*)(keys + B * kFlashKeys + i * 1024), 16,
                                                (uint32_t)(p + r) * 256 + 16 * (n ^ (r & 15)), 0, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);  // the keys' wait below counts the values' loads as the later ones
     // values of step k = 4 kk + i: positions 16 kk + 4 j + i
 #pragma unroll
     for (int k = 0; k < kLoads; ++k)
@@ -626,13 +632,14 @@ __device__ __forceinline__ void flash_block(
     for (int e = 0; e < 8; ++e) o[e] = float4_t{(float)v[e], (float)v[e], (float)v[e], (float)v[e]};
   }
 
-  // One step: `B` the buffers that hold it, `next` the number of load
-  // instructions issued after its own.
-  auto step = [&](auto bc, int p, bool more) {
+  // One step: B the buffers that hold it, MORE whether the next step's loads
+  // are in flight (compile-time, so that the waits for this step's values,
+  // which the compiler counts, leave them in flight).
+  auto step = [&](auto bc, auto mc, int p) {
     constexpr int B = decltype(bc)::value;
+    constexpr bool MORE = decltype(mc)::value;
     __builtin_amdgcn_sched_barrier(0);
-    if (more) wait_vmcnt<3 * kLoads>();  // the keys: this step's values and the next step's loads may be outstanding
-    else wait_vmcnt<kLoads>();
+    wait_vmcnt<(MORE ? 3 : 1) * kLoads>();  // the keys: this step's values and the next step's loads may be outstanding
     __builtin_amdgcn_sched_barrier(0);
     float sc[2][4];
 #pragma unroll
@@ -667,6 +674,7 @@ __device__ __forceinline__ void flash_block(
     u32x4 pa[4];
     const uint32_t a = probs + n * kFlashRow + 16 * j;  // lane (m, j): positions 16 kk + 4 j .. + 3 of head m
     lds_read4(pa, a, a + 64, a, a + 64);
+    __builtin_amdgcn_sched_barrier(0);  // no value is waited for before the softmax is done
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
       const u32x4 pk = pa[k >> 2];
@@ -678,14 +686,22 @@ __device__ __forceinline__ void flash_block(
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  for (int p = p_first; p < p_end; p += 2 * kStride) {
-    const bool more = p + kStride < p_end;
-    if (more) request(std::integral_constant<int, 1>{}, p + kStride);
-    step(std::integral_constant<int, 0>{}, p, more);
-    if (more) {
-      const bool again = p + 2 * kStride < p_end;
-      if (again) request(std::integral_constant<int, 0>{}, p + 2 * kStride);
-      step(std::integral_constant<int, 1>{}, p + kStride, again);
+  constexpr std::integral_constant<int, 0> b0;
+  constexpr std::integral_constant<int, 1> b1;
+  if (p_first < p_end) {
+    int p = p_first;
+    for (; p + 2 * kStride < p_end; p += 2 * kStride) {
+      request(b1, p + kStride);
+      step(b0, std::true_type{}, p);
+      request(b0, p + 2 * kStride);
+      step(b1, std::true_type{}, p + kStride);
+    }
+    if (p + kStride < p_end) {
+      request(b1, p + kStride);
+      step(b0, std::true_type{}, p);
+      step(b1, std::false_type{}, p + kStride);
+    } else {
+      step(b0, std::false_type{}, p);
     }
   }
 
