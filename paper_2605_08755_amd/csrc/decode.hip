@@ -899,7 +899,19 @@ int attention_qkv_tile(int64_t Hkv, int64_t L) {
 // 20.5 -> 18.8; with few key/value heads the tile kernel's many records per
 // head cost it more: 4:2 at 8192 12.9 -> 11.7, 8:1 12.4 -> 11.6 and at
 // 32768 23.3 -> 15.9.
-bool long_context(int64_t Hkv, int64_t pos) { return pos >= (Hkv <= 2 ? 8192 : 12288); }
+//
+// A block of it fills a compute unit, so key/value heads past 128 have whole
+// rounds of blocks, of which the last one leaves units idle: 129:129 at 12288
+// 167 -> 187 us (half of the units work), 300:300 381 -> 453, 342:342 437 -> 457,
+// 520:520 658 -> 713, 144:144 183 -> 187, but 150:150 195 -> 188, 384:384 485 -> 460.  With eight query heads
+// per key/value head the tile kernel's vector work is the longer one all the
+// same: 1120:140 251 -> 191, 2560:320 564 -> 465.
+bool attention_long_context(int64_t Hq, int64_t Hkv, int64_t pos) {
+  if (pos < (Hkv <= 2 ? 8192 : 12288)) return false;
+  if (Hkv <= 128 || Hq >= 8 * Hkv) return true;
+  const int64_t rounds = (Hkv + 255) / 256;
+  return rounds == 1 ? Hkv >= 150 : 4 * Hkv >= 3 * 256 * rounds;
+}
 
 int64_t decode_attention_qkv_tiles(int64_t Hkv, int64_t L) {
   const int P = attention_qkv_tile(Hkv, L);
@@ -916,7 +928,7 @@ hipError_t launch_decode_attention_qkv(const uint16_t* qkv, const uint16_t* qw, 
   e2.stop = ev.stop;
   const int R = (int)(Hq / Hkv);
   const float* cs = cos_sin + pos * kHeadDim;
-  if (long_context(Hkv, pos)) {
+  if (attention_long_context(Hq, Hkv, pos)) {
     // About one block per compute unit, its waves taking the same number of steps.
     const int64_t blocks = std::max<int64_t>(1, 256 / Hkv);  // per key/value head
     const int64_t unit = kFlashWaves * kFlashStep;

@@ -1,5 +1,6 @@
-"""The library's choice of kernel for a matrix-core linear, asked on the host
-(no GPU): the C++ functions behind laq_linear_*, by their mangled names."""
+"""The library's choice of kernel for a matrix-core linear or for the fused decode
+attention, asked on the host (no GPU): the C++ functions behind the entry
+points, by their mangled names."""
 import ctypes
 
 from paper_2605_08755_amd import laq
@@ -44,3 +45,9 @@ def group_quad_wave(M, tiles, nq):
     64 registers), or -1: the kernel whose waves walk several quads."""
     i = ctypes.c_int
     return _bind("_ZN3laq20mfma_group_quad_waveEili", i, i, ctypes.c_int64, i)(M, tiles, nq)
+
+
+def attention_long(Hq, Hkv, pos):
+    """Whether the fused attention runs in the long-context kernel."""
+    l = ctypes.c_int64
+    return _bind("_ZN3laq22attention_long_contextElll", ctypes.c_bool, l, l, l)(Hq, Hkv, pos)

@@ -1,11 +1,13 @@
-"""The long-context attention kernel's loads and waits as compiled for gfx950, on
-the host (the compiler's assembly of this repository's source, no GPU)."""
+"""The long-context attention kernel on the host (no GPU): which calls it takes,
+and its loads and waits as compiled for gfx950 (the compiler's assembly of this
+repository's source)."""
 import re
 import subprocess
 
 import pytest
 
 from paper_2605_08755_amd import build
+from routes import attention_long
 
 LOADS = 8  # load instructions of one step's keys, and of its values
 
@@ -38,3 +40,16 @@ def test_next_step_stays_in_flight(assembly, R):
     assert loads == 2 * (LOADS * ["K"] + LOADS * ["V"])
     waits = [e for e in events if isinstance(e, int)]
     assert waits.count(3 * LOADS) == 2 and min(waits) >= 2 * LOADS, events
+
+
+# (query heads, key/value heads, pos) -> kernel: both sides of the measured lines.
+@pytest.mark.parametrize("shape,long", [
+    ((2, 2, 8191), False), ((2, 2, 8192), True), ((32, 8, 12287), False), ((32, 8, 12288), True),
+    ((128, 128, 12288), True), ((129, 129, 12288), False), ((516, 129, 40000), False), ((1032, 129, 12288), True),
+    ((149, 149, 12288), False), ((150, 150, 12288), True), ((256, 256, 12288), True), ((300, 300, 12288), False),
+    ((383, 383, 12288), False), ((384, 384, 12288), True), ((520, 520, 12288), False), ((2560, 320, 12288), True),
+])
+def test_long_context_lines(shape, long):
+    """More than 128 key/value heads: only where the last round of blocks, one
+    to a compute unit, still fills the chip."""
+    assert attention_long(*shape) == long
