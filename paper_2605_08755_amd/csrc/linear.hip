@@ -1414,10 +1414,10 @@ template <int BITS>
 hipError_t launch_linear_group(LinearCall* calls, int count, int M, hipStream_t stream, const LaunchEvents& ev) {
   int G_max = 1;
   for (int i = 0; i < count; ++i) G_max = max(G_max, calls[i].G);
-  const int MT = ceil_pow2(M);
   // Matrix cores from kMfmaMinM activation rows on.
   if (M >= kMfmaMinM)
     return launch_linear_mfma_group<BITS>(calls, count, M, stream, ev);
+  const int MT = M;  // 1 or 2
   const int NT = G_max <= 32 ? 256 : (G_max <= 64 ? 512 : 1024);
   const int XB = (MT * G_max * 16 <= 2 * NT) ? 2 : 5;
   size_t lds = 0;
@@ -1434,7 +1434,7 @@ hipError_t launch_linear_group(LinearCall* calls, int count, int M, hipStream_t 
   }
   grp.count = count;
   grp.blocks = (int)blocks;
-  if (MT > 4 || lds > 64 * 1024) {
+  if (lds > 64 * 1024) {
     if (M >= 2) return launch_linear_mfma_group<BITS>(calls, count, M, stream, ev);
     // One activation row too long for LDS: one launch per call.
     for (int i = 0; i < count; ++i) {
@@ -1460,10 +1460,10 @@ hipError_t launch_linear_group(LinearCall* calls, int count, int M, hipStream_t 
 #define LAQ_FLAT_GX(MTV)           \
   if (XB == 2) LAQ_FLAT_GN(MTV, 2); \
   else LAQ_FLAT_GN(MTV, 5);
-  switch (MT) {
-    case 1: LAQ_FLAT_GX(1); break;
-    case 2: LAQ_FLAT_GX(2); break;
-    default: LAQ_FLAT_GX(4); break;
+  if (MT == 1) {
+    LAQ_FLAT_GX(1);
+  } else {
+    LAQ_FLAT_GX(2);
   }
 #undef LAQ_FLAT_GX
 #undef LAQ_FLAT_GN

@@ -256,9 +256,9 @@ __device__ __forceinline__ void mfma_block(
 }
 
 // ---------------------------------------------------------------------------
-// Activation-sharing variant for many row tiles and rows longer than five
-// quads (K > 2560).  A block of TB waves owns TB
-// consecutive 16-row tiles, one per wave, and walks K one quad (4 groups =
+// Activation-sharing variant for many row tiles and rows that the streaming
+// kernel does not take (more than 16 quads, or 1024 tiles of shorter rows).
+// A block of TB waves owns TB consecutive 16-row tiles, one per wave, and walks K one quad (4 groups =
 // 512 columns) at a time.  The quad's activation slab x[0..15][512q ..
 // 512q+511] (rows past M read as zero) goes straight from memory into LDS
 // (16-byte direct-to-LDS buffer loads, no registers), once per block for its
@@ -1135,10 +1135,10 @@ hipError_t launch_linear_mfma(const uint16_t* x, const uint32_t* qweight, const 
       else if (MT == 8) LAQ_QW(8, false, false, quad_lds);
       else LAQ_QW(16, false, false, quad_lds);
       break;
-    case MfmaRoute::QuadWaveRegs:
+    case MfmaRoute::QuadWaveRegs:  // M <= 8: above, so many units stream or share their slabs
       if (MT == 4) LAQ_QW(4, true, false, quad_lds);
       else if (MT == 8) LAQ_QW(8, true, false, quad_lds);
-      else LAQ_QW(16, true, false, quad_lds);
+      else return hipErrorInvalidValue;
       break;
     case MfmaRoute::QuadWaveCodes:
       if (MT == 4) LAQ_QW(4, false, true, quad_codes_lds);

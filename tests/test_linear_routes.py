@@ -40,6 +40,7 @@ def test_routes_are_consistent():
             elif r.startswith("quad_wave"):
                 unit = nq * (bits * 1024 + 512) if r == "quad_wave_codes" else 0
                 assert nq <= 10 and nq * MT * 1024 + unit <= LDS, case
+                assert r != "quad_wave_regs" or M <= 8, case
                 assert r != "quad_wave_codes" or tiles <= 256 * (LDS // (nq * MT * 1024 + unit)), case
             elif r in ("walk4", "walk8"):
                 assert tiles >= (3072 if r == "walk8" else 1024), case
