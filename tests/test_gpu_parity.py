@@ -16,7 +16,7 @@ import torch
 import oracle
 from oracle.compare import linear_check
 from paper_2605_08755_amd import inputs, laq
-from routes import group_quad_wave
+from routes import group_quad_wave, route, split_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -376,15 +376,18 @@ QUAD_WAVE_SHAPES = [(17, 128), (300, 640), (1030, 2560), (257, 4992), (4100, 512
 @pytest.mark.parametrize("bits", [3, 4])
 @pytest.mark.parametrize("N,K", QUAD_WAVE_SHAPES)
 def test_matrix_core_quad_wave(bits, N, K):
-    """Rows of at most 10 quads: one 16-row tile per block, one wave per quad.
-    A single group (K = 128), a partial last quad (K = 640, five groups;
-    K = 4992, 39 groups, ten quads), ten full quads (K = 5120), a ragged last
-    tile (N = 17, 300, 1030, 257, 4100), at least 1024 tiles (N = 16400, the
-    kernel keeps them up to M = 8), more waves than stay resident with the
-    fragments read up front (N = 10256, K = 4992: 641 tiles x 10 waves, the
-    64-register form), and K = 5248 (eleven quads: just past the kernel's
-    limit).  M from 3 (four-row slab; rows of at most 24 groups
-    included) to 16 (sixteen-row slab)."""
+    """Rows of at most 10 quads: one 16-row tile per block, one wave per quad, with
+    the codes through LDS or in registers.  A single group (K = 128), a partial
+    last quad (K = 640, five groups; K = 4992, 39 groups, ten quads), ten full
+    quads (K = 5120), a ragged last tile (N = 17, 300, 1030, 257, 4100), at least
+    1024 tiles (N = 16400; above M = 8, in W3 above 4, three tiles per block
+    instead), more waves than stay resident with the fragments read up front
+    (N = 10256, K = 4992: 641 tiles x 10 waves, the 64-register form up to M = 8,
+    the streaming kernel above), and K = 5248 (eleven quads: just past the
+    kernel's limit).  M from 3 (four-row slab) to 16 (sixteen-row slab)."""
+    assert {route(3, 4, 257, 4992), route(4, 4, 17, 128)} == {"quad_wave_codes"}
+    assert {route(3, 4, 1030, 2560), route(4, 16, 257, 4992)} == {"quad_wave"}
+    assert {route(bits, M, 10256, 4992) for M in (3, 8)} == {"quad_wave_regs"}
     say("mfma quad wave", bits, N, K)
     w = inputs.weights(N, K, cfg=22, layer=bits, proj=K % 97)
     codes, qw, s, z = oracle_packed(w, bits)
@@ -430,7 +433,8 @@ def test_matrix_core_two_tiles_ragged(bits):
     say("mfma two tiles", bits, N, K)
     w = inputs.weights(N, K, cfg=16, layer=bits)
     codes, qw, s, z = oracle_packed(w, bits)
-    for M in (3, 8, 16):
+    for M in (3, 5, 8, 16):
+        assert route(bits, M, N, K) == ("one_tile_codes" if M == 3 else "two_tiles")
         x = inputs.activations(M, K, cfg=16, layer=M)
         y = gpu_linear(x, qw, s, z, bits)
         r = linear_check(y, oracle.linear(x, codes, s, z))
@@ -440,12 +444,12 @@ def test_matrix_core_two_tiles_ragged(bits):
 @pytest.mark.parametrize("bits", [3, 4])
 @pytest.mark.parametrize("N,K", [(16404, 640), (16400, 128), (16448, 2560)])
 def test_matrix_core_shared_slab(bits, N, K):
-    """Enough 16-row tiles (>= 1024) and M > 8 for blocks of four tiles
-    sharing the activation slabs through LDS (K <= 2560: all quads in one
-    round trip): a last block with a partial tile and idle waves (N = 16404 =
-    1025 * 16 + 4), a partial last 4-group quad (K = 640, five groups) and a
-    single group (K = 128).  M = 2, 3 and 8 take the other kernels on the
-    same weights."""
+    """Enough 16-row tiles (>= 1024) for blocks of three tiles sharing the
+    activation slabs (M > 8; in W3 M > 4): a last block with idle waves and a
+    partial tile (N = 16404 = 1025 * 16 + 4), a partial last 4-group quad (K =
+    640, five groups) and a single group (K = 128).  M = 2, 3 and, in W4, 8 take
+    the other kernels on the same weights."""
+    assert route(bits, 9, N, K) == "share" and (route(bits, 8, N, K) == "share") == (bits == 3)
     say("mfma shared slab", bits, N, K)
     w = inputs.weights(N, K, cfg=17, layer=bits, proj=K % 97)
     codes, qw, s, z = oracle_packed(w, bits)
@@ -456,79 +460,68 @@ def test_matrix_core_shared_slab(bits, N, K):
         assert r["ok"], (M, r)
 
 
+def _check_walk(bits, N, K):
+    """Repeated weight rows against the oracle, equal rows bit for bit wherever
+    they lie, repeated calls bit for bit, nothing written past the output."""
+    codes, s, z, rows, w = _repeated_rows(bits, N, K)
+    for M in (3, 8, 16):
+        x = inputs.activations(M, K, cfg=19, layer=M)
+        ybuf = torch.full((M * N + 64,), 3.0, dtype=torch.float16, device=DEV)
+        y = laq.linear(to_dev(x), *w, bits, out=ybuf[:M * N].view(M, N))
+        assert torch.equal(y, laq.linear(to_dev(x), *w, bits)) and torch.all(ybuf[M * N:] == 3.0), M
+        y = y.cpu().numpy()
+        assert np.array_equal(y, y[:, rows]), M
+        r = linear_check(y[:, :len(codes)], oracle.linear(x, codes, s, z))
+        assert r["ok"], (M, r)
+
+
+# 17, 18 and 19 quads (every remainder of the loop over three register sets);
+# 73 and 71 groups: a partial last quad.
+WALK_K = [8704, 9088, 9344]
+
+
 @pytest.mark.parametrize("bits", [3, 4])
-@pytest.mark.parametrize("K", [3072, 4096])
+@pytest.mark.parametrize("K", WALK_K)
 def test_matrix_core_walk_four_tiles(bits, K):
-    """1024..3071 row tiles at M > 8 walk K in blocks of four tiles, the quad
-    weights in three register sets in turn: K = 3072 (6 quads, the unrolled
-    loop ends exactly) and 4096 (8 quads, two quads after the loop); N =
-    16400 = 1025 * 16 (a last block with one tile).  M = 3 takes the
-    one-wave-per-quad kernel on the same weights.  Sampled rows and the last
-    rows."""
+    """1024..3071 row tiles of more than 16 quads walk K in blocks of four tiles,
+    the quad weights in three register sets in turn.  N = 16400 = 1025 * 16: a
+    last block with one tile."""
     N = 16400
     say("mfma walk four tiles", bits, N, K)
-    rng = np.random.default_rng(K + bits)
-    w = inputs.weights(N, K, cfg=19, layer=bits, proj=K % 97)
-    rows = np.concatenate([np.sort(rng.choice(N - 16, 48, replace=False)), np.arange(N - 16, N)])
-    codes, qw, s, z = oracle_packed(np.ascontiguousarray(w[rows]), bits)
-    wd = to_dev(w)
-    q, sd, zd = laq.quantize(wd, bits)
-    del wd
-    torch.cuda.synchronize()
-    assert np.array_equal(q[rows].cpu().numpy().view(np.uint32), qw)
-    for M in (3, 12, 16):
-        x = inputs.activations(M, K, cfg=19, layer=M)
-        y = laq.linear(to_dev(x), q, sd, zd, bits)
-        torch.cuda.synchronize()
-        r = linear_check(y.cpu().numpy()[:, rows], oracle.linear(x, codes, s, z))
-        assert r["ok"], (M, r)
-    del q, sd, zd
+    assert {route(bits, M, N, K) for M in (3, 8, 16)} == {"walk4"}
+    _check_walk(bits, N, K)
 
 
 @pytest.mark.parametrize("M", [3, 5])
 def test_matrix_core_two_tiles_per_wave_small_m(M):
-    """Fewer than 1024 tiles, at least 256 of them and rows of more than 10
+    """More than 512 tiles (at M = 5 more than 256) and rows of more than 10
     quads: each wave takes two tiles, and its two KiB of partials reuse an
-    activation slab of only M rows.  N = 4100 (ragged), K = 6144 (12 quads)."""
-    N, K = 4100, 6144
+    activation slab of only M rows.  N = 8212 (ragged), K = 8704 (17 quads); rows
+    with the same weights give the same bits wherever they lie."""
+    N, K = 8212, 8704
     say("mfma two tiles per wave", M, N, K)
-    w = inputs.weights(N, K, cfg=20, layer=M)
+    assert route(3, M, N, K) == "two_tiles"
+    codes, s, z, rows, w = _repeated_rows(3, N, K)
     x = inputs.activations(M, K, cfg=20, layer=M)
-    codes, qw, s, z = oracle_packed(w, 3)
-    y = gpu_linear(x, qw, s, z, 3)
-    r = linear_check(y, oracle.linear(x, codes, s, z))
+    y = laq.linear(to_dev(x), *w, 3).cpu().numpy()
+    assert np.array_equal(y, y[:, rows])
+    r = linear_check(y[:, :len(codes)], oracle.linear(x, codes, s, z))
     assert r["ok"], r
 
 
-def test_matrix_core_walk_ragged():
-    """From 3072 row tiles at M > 8, blocks of eight tiles walk K one quad at
-    a time (K > 2560): N = 49168 = 3073 * 16 (a last block with one tile),
-    K = 3200 (25 groups: a partial last quad).  M = 3 and 8 take the
-    one-wave-per-quad kernel on the same weights.  Quantize on the GPU; codes
-    and outputs checked on sampled rows and the last rows."""
-    N, K = 49168, 3200
-    say("mfma walk ragged", N, K)
-    rng = np.random.default_rng(49)
-    w = inputs.weights(N, K, cfg=18, layer=3, proj=7)
-    rows = np.concatenate([np.sort(rng.choice(N - 16, 80, replace=False)), np.arange(N - 16, N)])
-    codes, qw, s, z = oracle_packed(np.ascontiguousarray(w[rows]), 3)
-    wd = to_dev(w)
-    q, sd, zd = laq.quantize(wd, 3)
-    del wd
-    torch.cuda.synchronize()
-    assert np.array_equal(q[rows].cpu().numpy().view(np.uint32), qw)
-    for M in (3, 8, 11, 16):
-        x = inputs.activations(M, K, cfg=18, layer=M)
-        y = laq.linear(to_dev(x), q, sd, zd, 3)
-        torch.cuda.synchronize()
-        r = linear_check(y.cpu().numpy()[:, rows], oracle.linear(x, codes, s, z))
-        assert r["ok"], (M, r)
-    del q, sd, zd
-    torch.cuda.empty_cache()
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("K", WALK_K)
+def test_matrix_core_walk_ragged(bits, K):
+    """From 3072 row tiles, blocks of eight tiles: N = 49173 = 3073 * 16 + 5, a
+    last block with one whole and one partial tile."""
+    N = 49173
+    say("mfma walk ragged", bits, N, K)
+    assert {route(bits, M, N, K) for M in (3, 8, 16)} == {"walk8"}
+    _check_walk(bits, N, K)
 
 
-STREAM_SHAPES = [(8200, 8192, (3, 8, 16)), (9003, 6528, (4, 9)), (26003, 2176, (8, 16)), (65541, 2560, (3, 16)),
-                 (16389, 3968, (8, 12)), (24581, 4096, (4, 5)), (10241, 5120, (8, 13))]
+STREAM_SHAPES = [(8200, 8192, (3, 8, 16)), (9003, 6528, (4, 9)), (80003, 2176, (3, 8, 16)), (65541, 2560, (3, 16)),
+                 (33013, 3968, (8, 12)), (24581, 4096, (4, 5)), (10241, 5120, (8, 13))]
 
 
 @pytest.mark.parametrize("bits", [3, 4])
@@ -543,6 +536,7 @@ def test_matrix_core_stream(bits, N, K, Ms):
     tiles.  Sampled rows and the last rows against the oracle; repeated calls
     bit-identical; nothing written past the output."""
     say("mfma stream", bits, N, K)
+    assert {route(bits, M, N, K) for M in Ms} == {"stream"}
     rng = np.random.default_rng(N + bits)
     w = inputs.weights(N, K, cfg=24, layer=bits, proj=K % 97)
     rows = np.concatenate([np.arange(16), np.sort(rng.choice(N - 64, 48, replace=False)) + 16, np.arange(N - 40, N)])
@@ -561,7 +555,7 @@ def test_matrix_core_stream(bits, N, K, Ms):
 
 # Shapes of the streaming kernel: every count of staged rows and staging phase,
 # split into K ranges, whole and partial lines.
-STREAM_ROUND_SHAPES = [(8200, 8192), (10241, 5120), (26213, 2176), (24581, 4096), (1030, 20608)]
+STREAM_ROUND_SHAPES = [(8200, 8192), (10241, 5120), (80003, 2176), (24581, 4096), (1600, 25216)]
 
 
 def _repeated_rows(bits, N, K, period=251):
@@ -582,10 +576,12 @@ def test_matrix_core_stream_rounding(bits, N, K):
     off by up to 2^-25 of the sum so far, in random directions: about 1e-6 of
     the output's RMS for the longest row, and an error e moves a value across a
     rounding boundary with probability 2 |e| / ulp, where the ulp is 7e-4 of a
-    typical value: 0.2 %.  Bound: 0.5 %.  Activations of both signs, one-signed,
+    typical value: 0.2 %.  Bound: 0.5 %.  (5120-wide rows below M = 8 take the
+    one-wave-per-quad kernel.)  Activations of both signs, one-signed,
     subnormal and up to the largest halves.  Rows with the same weights give
     the same bits wherever they lie."""
     say("mfma stream rounding", bits, N, K)
+    assert {route(bits, M, N, K, True) for M in (8, 16)} <= {"stream", "split_stream"}
     codes, s, z, rows, (qd, sd, zd) = _repeated_rows(bits, N, K)
     P = len(codes)
     for kind, xscale, sscale in (("both signs", 1.0, 1.0), ("one sign", 1.0, 1.0), ("subnormal", 2.0**-17, 2.0**6),
@@ -610,7 +606,8 @@ def test_matrix_core_stream_rounding(bits, N, K):
 
 
 @pytest.mark.parametrize("bits", [3, 4])
-@pytest.mark.parametrize("N,K", [(200, 640), (100, 16384)] + STREAM_ROUND_SHAPES)
+@pytest.mark.parametrize("N,K", [(200, 640), (100, 16384), (16437, 2176), (16400, 8704), (4100, 9728), (731, 22272)] +
+                         STREAM_ROUND_SHAPES)
 def test_matrix_core_infinite_activation(bits, N, K):
     """One infinite activation: its row's outputs are infinite with the sign of
     (q - z) x, or NaN where q = z, on every matrix-core path alike; the other
@@ -631,18 +628,26 @@ def test_matrix_core_infinite_activation(bits, N, K):
             assert np.array_equal(got, ref, equal_nan=True), (M, row, col)
 
 
-SPLIT_SHAPES = [(5120, 25600), (100, 25088), (3, 20608), (1030, 20480)]
+SPLIT_SHAPES = [(5120, 25600), (100, 25088), (3, 20608), (1030, 20480), (1030, 20608), (1600, 25216), (731, 22272),
+                (190, 131840), (250, 131840), (380, 131840)]
 
 
 @pytest.mark.parametrize("bits", [3, 4])
 @pytest.mark.parametrize("N,K", SPLIT_SHAPES)
 def test_split_k(bits, N, K):
-    """K split across workgroups of four row tiles (rows of >= 40 quads, fewer
-    than 1024 tiles): the Qwen3-32B down projection (ranges of five quads), a
-    partial last quad (K = 25088: 196 groups; K = 20608: 161), a last block
-    with idle tiles (N = 100, 1030) and a single partial tile (N = 3), ranges
-    of one quad; against the oracle, deterministic, and the plain entry point
-    also within tolerance."""
+    """K split across workgroups (rows of >= 40 quads, fewer than 1024 tiles).
+    With many (tile, quad) units the ranges run in the streaming kernel: the
+    Qwen3-32B down projection, 1030 rows (at M = 16 in W4 only), and odd group
+    counts (K = 20608: 161, 25216: 197) with part lines, a partial last quad and
+    quads past the row in the last range.  Otherwise blocks of four tiles over
+    ranges of one (N = 100, 3), two (731), three, four and five (K = 131840) quads,
+    with idle tiles in the last block and a partial tile; against the oracle,
+    deterministic, and the plain entry point also within tolerance."""
+    ranges = {100: 1, 3: 1, 731: 2, 190: 3, 250: 4, 380: 5}.get(N)
+    if ranges:
+        assert split_plan(16, N, K // 128).qs == ranges and route(bits, 16, N, K, True) == "split"
+    else:
+        assert route(bits, 8, N, K, True) == "split_stream"
     say("split K", bits, N, K)
     assert laq.workspace_bytes(16, N, K) > 0
     w = inputs.weights(N, K, cfg=19, layer=bits, proj=K % 83)
@@ -799,9 +804,11 @@ GRAPH_CASES = [
     ("matrix cores one wave per quad M=16", 16, 300, 5120, 3),
     ("matrix cores one wave per quad, 64 registers M=4", 4, 10256, 4992, 3),
     ("matrix cores one tile M=5", 5, 1030, 9728, 4),
-    ("matrix cores four tiles M=16", 16, 16400, 2560, 3),
-    ("matrix cores walk M=12", 12, 16400, 4096, 3),
+    ("matrix cores three tiles M=16", 16, 16400, 2560, 3),
+    ("streaming M=12", 12, 16400, 4096, 3),
+    ("matrix cores walk M=12", 12, 16400, 8704, 3),
     ("split K with workspace M=16", 16, 1030, 25600, 3),
+    ("split K, streaming ranges M=16", 16, 1600, 25216, 3),
 ]
 
 
