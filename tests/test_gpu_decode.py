@@ -135,12 +135,15 @@ def test_decode_attention_qkv(Hq, Hkv, pos, S):
 
 @pytest.mark.parametrize("Hq,Hkv,pos,S", [(32, 8, 12288, 12300), (4, 4, 13055, 13056), (4, 4, 12543, 12600),
                                            (64, 8, 12801, 12802), (2, 1, 8192, 8200), (8, 1, 8225, 8400),
-                                           (2, 2, 8448, 8449), (1, 1, 20000, 20001), (16, 4, 16383, 16384)])
+                                           (2, 2, 8448, 8449), (1, 1, 20000, 20001), (16, 4, 16383, 16384),
+                                           (16, 16, 12288, 12300), (32, 16, 12900, 13000), (24, 24, 12500, 12501),
+                                           (32, 32, 14000, 14001)])
 def test_decode_attention_qkv_long(Hq, Hkv, pos, S):
     """The long-context kernel (from position 12288, or 8192 with at most two
     key/value heads): chunk and step edges (pos a multiple of 32 and 256, one
     below and one past it, a last chunk with one position and waves with no
-    step), 1 to 8 query heads per key/value head, against the oracle; rows past
+    step; one to five and seven steps per wave: the loop over two steps, and its
+    ends after one and two), 1 to 8 query heads per key/value head, against the oracle; rows past
     pos hold NaN and must not be read; rows other than pos stay untouched; the
     call is deterministic.  A large score late in the context moves the
     running maximum after most steps."""
