@@ -99,15 +99,20 @@ __host__ __device__ constexpr int mfma_block_waves(int M, int nq) {
 }
 
 // The same with the codes through LDS (request_quad), a unit per wave beside
-// its slab: as many waves as fit, at most 16 (8 at M > 8), and half the quads
-// where two rounds take them.  (Measured on MI355X, 19 quads: M = 8 10 waves 7.71 us, 13
-// waves 8.10; M = 16, three rounds, 8 waves 8.97, 7 waves 9.90.)
+// its slab: as many waves as fit, at most 16, above eight activation rows at most 8;
+// half the quads where two rounds take them, except with eight waves.  (Measured
+// on MI355X, 19 quads: M = 8 10 waves 7.71 us, 13 waves 8.10; M = 16, three rounds, 8
+// waves 8.97, 7 waves 9.90.  Two rounds at M > 8: 11 and 12 quads with six waves up to
+// 1.10 of the kernel without codes in LDS, with eight 0.89 - 0.98; W4 at M = 16, where
+// seven fit, 12 quads 0.83 - 1.05 with six and 0.85 - 1.10 with seven, 11 quads 0.93 and
+// 0.87.)
 __host__ __device__ constexpr int mfma_codes_waves(int bits, int M, int nq) {
   const int fit = kBlockLdsU4 * 16 / (M * 1024 + unit_bytes(bits));
   const int most = M > 8 ? 8 : 16;
   const int wmax = fit < most ? fit : most;
   const int rounds = (nq + wmax - 1) / wmax;
-  return rounds == 2 ? (nq + 1) / 2 : (wmax < nq ? wmax : nq);
+  const bool half = M <= 8 || (wmax < 8 && nq % 2 == 0);
+  return half && rounds == 2 ? (nq + 1) / 2 : (wmax < nq ? wmax : nq);
 }
 
 template <int BITS, int TW, bool CLDS>
