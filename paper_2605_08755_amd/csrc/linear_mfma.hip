@@ -1073,10 +1073,13 @@ MfmaRoute mfma_route(int bits, int M, int64_t N, int64_t K, bool workspace) {
     if (tiles * nq > (int64_t)kQuadWaveResident) return MfmaRoute::QuadWaveRegs;
     // Codes through LDS while the blocks that then fit on the compute units
     // still hold every tile at once; in W3 from eight quads (fewer: 536 x 768 at
-    // M = 9 2.91 -> 2.98 us, 1.00 - 1.02 of the register form up to seven quads).
+    // M = 9 2.91 -> 2.98 us, 1.00 - 1.02 of the register form up to seven quads), in
+    // W4 from two (one: 1280 x 128 at M = 4 2.90 -> 2.99).  Three blocks of five waves
+    // on a compute unit: 9472 x 2304 W4 at M = 3 5.78 -> 6.43, up to 1.14; of four or
+    // six waves 0.93 - 1.02.
     const size_t lds_codes = lds + (size_t)nq * unit_bytes(bits);
-    return (bits == 4 || nq >= 8) && tiles <= 256 * (int64_t)(kLds / lds_codes) ? MfmaRoute::QuadWaveCodes
-                                                                                 : MfmaRoute::QuadWave;
+    const int64_t resident = nq == 5 ? std::min<int64_t>(2, kLds / lds_codes) : kLds / lds_codes;
+    return nq >= (bits == 4 ? 2 : 8) && tiles <= 256 * resident ? MfmaRoute::QuadWaveCodes : MfmaRoute::QuadWave;
   }
   // Many tiles, longer rows: blocks of four or eight tiles walking K share
   // each activation slab through LDS.

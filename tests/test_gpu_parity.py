@@ -385,7 +385,7 @@ def test_matrix_core_quad_wave(bits, N, K):
     (N = 10256, K = 4992: 641 tiles x 10 waves, the 64-register form up to M = 8,
     the streaming kernel above), and K = 5248 (eleven quads: just past the
     kernel's limit).  M from 3 (four-row slab) to 16 (sixteen-row slab)."""
-    assert {route(3, 4, 257, 4992), route(4, 4, 17, 128)} == {"quad_wave_codes"}
+    assert {route(3, 4, 257, 4992), route(4, 4, 300, 640)} == {"quad_wave_codes"}
     assert {route(3, 4, 1030, 2560), route(4, 16, 257, 4992)} == {"quad_wave"}
     assert {route(bits, M, 10256, 4992) for M in (3, 8)} == {"quad_wave_regs"}
     say("mfma quad wave", bits, N, K)

@@ -97,6 +97,8 @@ LINES = [
     ((3, 16, 656, 25600, True), "split"), ((3, 8, 656, 25600, True), "split_stream"),
     ((3, 16, 1120, 25600, True), "split"), ((3, 16, 5120, 25600, True), "split_stream"),
     ((3, 16, 5120, 25600), "two_tiles"), ((3, 9, 536, 768), "quad_wave"), ((4, 9, 536, 768), "quad_wave_codes"),
+    ((4, 4, 1280, 512), "quad_wave"), ((4, 4, 1280, 640), "quad_wave_codes"),
+    ((4, 3, 8192, 2304), "quad_wave_codes"), ((4, 3, 8208, 2304), "quad_wave"), ((4, 3, 12288, 3072), "quad_wave_codes"),
     ((3, 4, 2560, 4096), "quad_wave_codes"),
     # codes in LDS, eight waves above M = 8: one block on a compute unit
     ((3, 9, 4096, 5376), "one_tile_codes"), ((3, 9, 4112, 5376), "two_tiles"),
