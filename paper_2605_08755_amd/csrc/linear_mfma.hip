@@ -990,6 +990,33 @@ SplitPlan mfma_split_plan(int M, int64_t N, int G) {
 
 namespace {
 
+// Whether linear_stream.hip takes rows of 11 to 16 quads, otherwise the kernel with two
+// tiles per block (measured on MI355X over 300 to 1023 tiles, W3 and W4, whole and part
+// lines, M = 3 .. 16, as ratios of the streaming kernel's time to that one's):
+//  - 513 to 768 tiles leave the other kernel's second round of 256 blocks half
+//    empty: 0.55 - 1.0.
+//  - Up to 512 tiles it has one round.  Above eight rows whole lines gain (0.83 -
+//    1.02; W3 with 14 quads, unevenly over the four SIMDs, up to 1.07), others
+//    do not (0.95 - 1.12).  Up to eight rows W4 0.8 - 1.02, W3 0.89 - 1.03 with an even
+//    count of quads and up to 1.05 with an odd one.
+//  - From 769 tiles its second round is full, and two blocks of it stay
+//    resident up to ten rows (a slab of M KiB per wave): W3 with 11, 13 and, above
+//    four rows, 14 quads 1.0 - 1.17 up to eight rows, 13 quads 1.15 at nine and ten;
+//    W4 with 11 quads 1.08 at nine and ten; the others 0.75 - 1.03, from eleven rows
+//    0.6 - 0.98.
+bool long_rows_pay(int bits, int M, int64_t tiles, int nq, int G) {
+  if (tiles * nq < 4096 || tiles <= 256) return false;
+  if (tiles <= 512) {
+    if (M > 8) return G % 8 == 0 && (bits == 4 || nq % 4 == 0);
+    return bits == 4 || nq % 2 == 0;
+  }
+  if (tiles > 768 && tiles < kMfmaShareMinTiles) {
+    if (M <= 8) return bits == 4 || nq == 12 || nq >= (M <= 4 ? 14 : 15);
+    if (M <= 10) return nq != (bits == 4 ? 11 : 13);
+  }
+  return true;
+}
+
 // Where keeping the activations in registers over many tiles (linear_stream.hip)
 // is the faster way: from a count of (tile, quad) units on, with which a block
 // walks several tiles.  The lines lie where the two ways cross, measured on
@@ -1006,17 +1033,18 @@ namespace {
 //    five quads 0.86 - 1.00 at 16384.
 //  - M <= 4: whole lines 0.8 - 1.0 at 12288; others W3 0.92 - 1.05 at 16384, below 1
 //    at 24576, nine quads 1.00 at 40000; W4 0.77 - 1.04 at 16384.
-//  - More than ten quads (no one-wave-per-quad kernel there): 0.8 - 1.0 from 4096
-//    units, once there are more tiles than compute units (256 tiles of 16 quads
-//    1.04 - 1.16, 257 0.83 - 0.92).
+//  - More than ten quads: long_rows_pay().
 //  - 1024 tiles are one round of the four-tiles-per-block kernel on 256 compute
 //    units, which only few shapes beat: W3 up to eleven quads and at 13 1.04 - 1.2
-//    (eight quads 0.96), W4 at M > 8 with nine and eleven quads 1.06 - 1.10.
+//    (eight quads 0.96), W4 at M > 8 with nine and eleven quads 1.06 - 1.10.  Two full
+//    rounds (1793 - 2048 tiles): W3 with a whole last quad of 9, 11 or 13 1.04 - 1.07 at
+//    M > 4, a partial one 0.93 - 1.01; 1700 tiles 0.99, 2100 0.86.
 bool stream_pays(int bits, int M, int64_t tiles, int nq, int G) {
   const int64_t units = tiles * nq;
   if (nq < 5) return false;
   if (tiles == kMfmaShareMinTiles && (bits == 3 ? nq < 12 || nq == 13 : M > 8 && (nq == 9 || nq == 11))) return false;
-  if (nq > kQuadWaveMax) return units >= 4096 && tiles > 256;
+  if (bits == 3 && M > 4 && G % 4 == 0 && nq >= 9 && nq <= 13 && nq % 2 && tiles > 1792 && tiles <= 2048) return false;
+  if (nq > kQuadWaveMax) return long_rows_pay(bits, M, tiles, nq, G);
   if (M > 8) return units >= (nq > 5 ? 4096 : bits == 4 && G % 4 ? 24576 : 8192);
   const bool whole = G % 8 == 0;
   if (M > 4) {

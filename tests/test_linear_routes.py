@@ -100,8 +100,18 @@ LINES = [
     ((4, 4, 1280, 512), "quad_wave"), ((4, 4, 1280, 640), "quad_wave_codes"),
     ((4, 3, 8192, 2304), "quad_wave_codes"), ((4, 3, 8208, 2304), "quad_wave"), ((4, 3, 12288, 3072), "quad_wave_codes"),
     ((3, 4, 2560, 4096), "quad_wave_codes"),
+    ((3, 9, 32768, 4608), "walk4"), ((3, 9, 32784, 4608), "stream"), ((3, 8, 29600, 5632), "walk4"),
+    ((3, 16, 28672, 6656), "stream"), ((3, 16, 28688, 6656), "walk4"), ((3, 16, 28688, 6528), "stream"),
     # codes in LDS, eight waves above M = 8: one block on a compute unit
     ((3, 9, 4096, 5376), "one_tile_codes"), ((3, 9, 4112, 5376), "two_tiles"),
+    # 11 to 16 quads: up to 512 tiles, to 768, below 1024
+    ((3, 10, 8192, 5376), "two_tiles"), ((3, 12, 5376, 7680), "two_tiles"), ((4, 9, 8192, 7680), "two_tiles"),
+    ((3, 9, 8192, 8192), "stream"), ((3, 9, 8192, 7168), "two_tiles"), ((4, 9, 8192, 7168), "stream"),
+    ((3, 8, 8192, 7680), "two_tiles"), ((4, 8, 8192, 7680), "stream"), ((3, 8, 8192, 7040), "stream"),
+    ((3, 10, 8208, 5376), "stream"), ((3, 5, 12288, 5504), "stream"), ((3, 5, 12304, 5504), "two_tiles"),
+    ((3, 3, 15104, 6528), "two_tiles"), ((3, 4, 15104, 7168), "stream"), ((3, 5, 15104, 7168), "two_tiles"),
+    ((3, 5, 15104, 7680), "stream"), ((3, 10, 15104, 6528), "two_tiles"), ((3, 11, 15104, 6528), "stream"),
+    ((4, 10, 15104, 5504), "two_tiles"), ((4, 11, 15104, 5504), "stream"), ((4, 8, 15104, 5504), "stream"),
 ]
 
 
