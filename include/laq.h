@@ -176,7 +176,7 @@ laq_status laq_linear_w3g128(const void *x, const uint32_t *qweight,
  * (N <= 16368): there, a workgroup reads a range of the activations once for
  * many tiles and the K ranges give every compute unit work, which outweighs
  * the second kernel (measured on MI355X: Qwen3-32B down projection, N = 5120,
- * K = 25600, M = 16: 33.2 us in one piece, 19.8 us split).  Returns 0 when the call
+ * K = 25600, M = 16: 33.2 us in one piece, 21.1 us split).  Returns 0 when the call
  * never splits K (then the _ws entry point is the plain one), otherwise an
  * upper bound of what the call uses.  Depends on the shape only (not on the
  * bit width); an invalid shape gives 0.
@@ -498,9 +498,10 @@ int64_t laq_decode_attention_qkv_workspace_bytes(int64_t Hq, int64_t Hkv, int64_
  *   out[h] = sum_{t <= pos} softmax_t(q[h] . k[t] / sqrt(128)) v[t]
  * (fp16 [Hq][128]) with q rounded to fp16 as laq_qk_norm_rope_f16 stores it.
  * The positions are split into tiles of 16, 32 or 64 (so that short contexts
- * still occupy the GPU), whose partial results go to the workspace and are
- * combined in position order.  Results: within the tolerance of the
- * two-call sequence (the tiles differ), deterministic.
+ * still occupy the GPU) or, in long contexts (from pos = 12288, or 8192 with at
+ * most two key/value heads), into up to 256 / Hkv chunks, whose partial results
+ * go to the workspace and are combined in position order.  Results: within the
+ * tolerance of the two-call sequence (the tiles differ), deterministic.
  *   workspace  [scratch] device memory, 16-byte aligned, any contents, at
  *              least laq_decode_attention_qkv_workspace_bytes(Hq, Hkv, pos + 1)
  *              bytes; calls in flight need separate workspaces.
