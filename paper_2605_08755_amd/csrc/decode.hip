@@ -478,9 +478,9 @@ __global__ __launch_bounds__(64 * R) void attn_qkv_partial_kernel(
 // The next step's loads are in flight while a step is computed: the waits count
 // instructions, so a step is compiled once with and once without later loads.
 // (Measured on MI355X against one form for both, which waited for all loads before
-// the value sums of every other step: 64:8 at 12288 21.4 -> 19.9 us, 32:8 at 32767
-// 33.5 -> 32.5, 8:1 at 16000 12.6 -> 12.1; with an odd count of steps per wave 32:8
-// at 24000 26.7 -> 27.4, 4:4 at 40000 24.0 -> 24.6.)
+// the value sums of every other step: 64:8 at 12288 21.4 -> 20.4 us, 32:8 at 32767
+// 33.8 -> 32.8, 8:1 at 16000 12.6 -> 12.2; with an odd count of steps per wave 32:8
+// at 24000 26.7 -> 27.6, 4:4 at 40000 24.1 -> 24.8.)
 // The token at pos is not read back from the cache: wave 0 of the last chunk
 // starts from it (maximum its score, denominator 1, value sums its value row).
 constexpr int kFlashWaves = 8;
@@ -606,6 +606,18 @@ __device__ __forceinline__ void flash_block(
     const uint32_t a = lds_byte(q16) + n * kHeadDim * 2 + 16 * j;
     lds_read4(qa, a, a + 64, a + 128, a + 192);
   }
+  // q . key of four heads and one position: a sum per window, added pairwise as
+  // the tile kernel adds its four accumulators.  (One running sum over the
+  // windows: up to 2 % faster, but 7 to 15 % more outputs than the tile kernel's
+  // that are not the rounding of the 64-bit result where scores are large.)
+  auto scores = [&](const u32x4(&f)[4]) {
+    float4_t c[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      c[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, qa[i]), __builtin_bit_cast(half8_t, f[i]),
+                                                    float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    return (c[0] + c[1]) + (c[2] + c[3]);
+  };
   constexpr float kScale = 0.08838834764831845f;  // 1 / sqrt(128)
   // Running state of head 4j + r: maximum, this lane's part of the
   // denominator, and value sums of dimensions 8n + e.
@@ -619,10 +631,7 @@ __device__ __forceinline__ void flash_block(
     u32x4 f[4];
     const uint32_t a = lds_byte(new_kv) + 16 * j;  // the key as every column
     lds_read4(f, a, a + 64, a + 128, a + 192);
-    float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, qa[i]), __builtin_bit_cast(half8_t, f[i]), c, 0, 0, 0);
+    const float4_t c = scores(f);
     const uint32_t b = lds_byte(new_kv) + kHeadDim * 2 + 16 * n;
     lds_read4(f, b, b, b, b);
     const half8_t v = __builtin_bit_cast(half8_t, f[0]);
@@ -647,10 +656,7 @@ __device__ __forceinline__ void flash_block(
       u32x4 f[4];
       const uint32_t a = lds_byte(keys + B * kFlashKeys) + (16 * t + n) * 256;
       lds_read4(f, a + 16 * (j ^ n), a + 16 * ((4 + j) ^ n), a + 16 * ((8 + j) ^ n), a + 16 * ((12 + j) ^ n));
-      float4_t c = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, qa[i]), __builtin_bit_cast(half8_t, f[i]), c, 0, 0, 0);
+      const float4_t c = scores(f);
       const bool valid = p + 16 * t + n < p_end;
 #pragma unroll
       for (int r = 0; r < 4; ++r) sc[t][r] = valid ? c[r] * kScale : -INFINITY;

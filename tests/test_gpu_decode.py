@@ -176,6 +176,35 @@ def test_decode_attention_qkv_long(Hq, Hkv, pos, S):
     assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
 
 
+def test_decode_attention_long_precision():
+    """Before its output's rounding the long-context kernel is no further from 64
+    bits than the two-kernel sequence on the same fp16 query and cache.  An
+    error e moves an output across a rounding boundary with probability 2 |e| /
+    ulp, so the shares of outputs that are not the fp16 rounding of the 64-bit
+    result compare the errors.  Large scores (about +-250), where the scores'
+    own rounding decides: 1157 of 245760 outputs for the sequence, 887 for the
+    long-context kernel with a sum per window of the scores (one running sum
+    over the windows: 1239), about 30 either way by chance."""
+    Hq, Hkv, pos, S = 32, 8, 12288, 12289
+    say("decode_attention_qkv long precision")
+    cs = dev(cos_sin_table(S))
+    g = torch.Generator(device=DEV).manual_seed(5)
+    rnd = lambda *shape: torch.randn(*shape, device=DEV, generator=g)
+    wrong = [0, 0]
+    for _ in range(60):
+        qkv = (2 * rnd((Hq + 2 * Hkv) * 128)).half()
+        qw, kw = (8 * (1 + 0.2 * rnd(128))).half(), (1 + 0.2 * rnd(128)).half()
+        kc, vc = rnd(Hkv, S, 128).half(), rnd(Hkv, S, 128).half()
+        q = laq.qk_norm_rope(qkv, qw, kw, cs, pos, Hq, Hkv, EPS, kc, vc)
+        two = laq.decode_attention(q, kc, vc, pos + 1)
+        one = laq.decode_attention_qkv(qkv, qw, kw, cs, pos, Hq, Hkv, EPS, kc, vc)
+        sc = torch.matmul(q.double().view(Hkv, Hq // Hkv, 128), kc.double().transpose(1, 2).contiguous()) / 128**0.5
+        ref = torch.matmul(sc.softmax(-1), vc.double()).view(Hq, 128).half()
+        for i, y in enumerate((two, one)):
+            wrong[i] += int((y.view(Hq, 128) != ref).sum())
+    assert wrong[1] <= wrong[0], wrong
+
+
 @pytest.mark.parametrize("M,I", [(1, 9728), (2, 100), (1, 25600)])
 def test_silu_mul(M, I):
     say("silu_mul", M, I)
