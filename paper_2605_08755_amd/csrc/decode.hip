@@ -4,6 +4,7 @@
 // key/value cache append, single-token attention over the cache, and
 // SiLU-and-multiply.  fp16 in and out, fp32 arithmetic, fixed reduction
 // orders (deterministic).  Head dimension 128.
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -664,10 +665,11 @@ __device__ __forceinline__ void flash_block(
     float alpha[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float mn = fmaxf(m[r], row_max(fmaxf(sc[0][r], sc[1][r])));  // finite: a step has a valid position
-      alpha[r] = expf(m[r] - mn);
+      const float mn = fmaxf(m[r], row_max(fmaxf(sc[0][r], sc[1][r])));
+      const float ref = fmaxf(mn, -FLT_MAX);  // every score so far -inf: weights of 0, not exp(-inf + inf)
+      alpha[r] = expf(m[r] - ref);
       m[r] = mn;
-      const float p0 = expf(sc[0][r] - mn), p1 = expf(sc[1][r] - mn);
+      const float p0 = expf(sc[0][r] - ref), p1 = expf(sc[1][r] - ref);
       l[r] = fmaf(l[r], alpha[r], p0 + p1);
       const uint32_t row = probs + (4 * j + r) * kFlashRow + 4 * n;
       lds_put(row, p0);
@@ -739,7 +741,7 @@ __device__ __forceinline__ void flash_block(
     float den = 0.0f, num = 0.0f;
 #pragma unroll
     for (int i = 0; i < kFlashWaves; ++i) {
-      const float e = expf(stat[(i * R + h) * 2] - M);  // a wave without positions: exp(-inf) = 0
+      const float e = expf(stat[(i * R + h) * 2] - fmaxf(M, -FLT_MAX));  // a wave without positions: exp(-inf) = 0
       den = fmaf(e, stat[(i * R + h) * 2 + 1], den);
       num = fmaf(e, osum[(i * R + h) * kHeadDim + d], num);
     }

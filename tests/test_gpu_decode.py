@@ -176,6 +176,27 @@ def test_decode_attention_qkv_long(Hq, Hkv, pos, S):
     assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
 
 
+@pytest.mark.parametrize("first,last", [(12320, 12320), (12288, 12320)])
+def test_decode_attention_long_infinite_scores(first, last):
+    """Keys whose scores are -inf weigh nothing, also where they are all that a
+    wave (position 12320) or a whole chunk's cached part has: the result is
+    that of the other positions, as in the kernel for shorter contexts."""
+    Hq, Hkv, pos, S = 4, 4, 12321, 12330
+    say("decode_attention_qkv long infinite scores", first, last)
+    rng = np.random.default_rng(first)
+    qkv = f16(rng, (Hq + 2 * Hkv) * 128, 2.0)
+    w = np.ones(128, np.float16)
+    Kc, Vc = f16(rng, (Hkv, S, 128)), f16(rng, (Hkv, S, 128))
+    q, k_new, v_new = OD.qk_norm_rope(qkv, w, w, pos, Hq, Hkv, 128, EPS, THETA)
+    Kc[:, first:last + 1, 5] = np.where(q[:, 5] > 0, -np.inf, np.inf)[:, None]
+    kc, vc = dev(Kc), dev(Vc)
+    out = laq.decode_attention_qkv(dev(qkv), dev(w), dev(w), dev(cos_sin_table(S)), pos, Hq, Hkv, EPS, kc, vc)
+    rest = np.r_[0:first, last + 1:pos + 1]
+    Kc[:, pos], Vc[:, pos] = kc[:, pos].cpu().numpy(), v_new
+    r = linear_check(out.cpu().numpy(), OD.decode_attention(q.astype(np.float16), Kc[:, rest], Vc[:, rest]))
+    assert r["ok"], r
+
+
 def test_decode_attention_long_precision():
     """Before its output's rounding the long-context kernel is no further from 64
     bits than the two-kernel sequence on the same fp16 query and cache.  An
